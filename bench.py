@@ -18,6 +18,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -39,10 +40,33 @@ def n_half_space(m):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "ewald_internal.h"):
+    for f in ("kernels.hip", "mesh.hip", "ewald_internal.h"):
         with open(os.path.join(ROOT, "paper_2408_03273_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
+
+
+def recip_flops(desc: str, kmax, nm: float, frames: int = 1):
+    """FP64 flops of the reciprocal sums over the MM charges, per kernel group:
+    algorithmic and executed.  Gridded sums (the plan names its mesh): each
+    charge meets 16^3 mesh points, one multiply-add per point when spread, two
+    (value and derivative) when read; the mesh is contracted with the real basis
+    of 2 m + 1 functions per axis, z, y, x, and back.  Dense sums, per (k in the
+    half space, MM charge): forward 4 (the folded method's minimal count: one
+    real multiply-add of Re/Im of q e^{i(kx x + ky y)} with cos and with sin of
+    p kz0 z per (column, |nz|) covers both k = (kx, ky, +-p kz0)), adjoint 6 (the
+    forces); executed by the matrix-core kernels 4 and 8 (the adjoint also forms
+    the potential, dE/dq, and the nz-weighted sums)."""
+    m = re.search(r"mesh=(\d+)x(\d+)x(\d+)", desc)
+    if m:
+        n0, n1, n2 = (int(v) for v in m.groups())
+        c0, c1, c2 = (2 * k + 1 for k in kmax)
+        contract = 2.0 * frames * (n0 * n1 * n2 * c2 + n0 * n1 * c1 * c2 + n0 * c0 * c1 * c2)
+        alg = {"mesh_sfac": 2.0 * 16 ** 3 * nm + contract, "mesh_force": 4.0 * 16 ** 3 * nm + contract}
+        return alg, alg
+    nh = n_half_space(kmax)
+    return ({"sfac_mm": 4.0 * nh * nm, "force_mm": 6.0 * nh * nm},
+            {"sfac_mm": 4.0 * nh * nm, "force_mm": 8.0 * nh * nm})
 
 
 def traffic_from_profiles(kernel: str, src_hash: str):
@@ -151,25 +175,19 @@ def main():
     ms_hot = timed_steps(pplan, args.steps)
     hot_kern = pplan.profile_report()
 
-    # roofline of the dominant hot kernel, from the events of the bracketed run.
-    # Algorithmic flops per (k in the half space, MM atom): forward 4 (the
-    # folded method's minimal count: one real multiply-add of Re/Im of
-    # q e^{i(kx x + ky y)} with cos and with sin of p kz0 z per (column, |nz|)
-    # covers both k = (kx, ky, +-p kz0)), adjoint 6 (the forces: the imaginary
-    # part of the product with the QM structure factor and the k-weighted
-    # accumulation).  Executed by the matrix-core kernels: 4 and 8 (the adjoint
-    # also forms the potential, dE/dq, and the nz-weighted sums).
+    # roofline of the dominant hot kernel group, from the events of the bracketed run
     per = {k: dict(count=v["count"], avg_us=1e3 * v["total_ms"] / max(v["count"], 1),
                    ms_per_step=v["total_ms"] / args.steps) for k, v in hot_kern.items()}
-    flops = {"sfac_mm": 4.0 * nh * s.nm, "force_mm": 6.0 * nh * s.nm}
-    executed = {"sfac_mm": 4.0 * nh * s.nm, "force_mm": 8.0 * nh * s.nm}
+    flops, executed = recip_flops(pplan.describe(), s.kmax, float(s.nm))
     hot = {k: per[k] for k in flops if k in per}
     dom = max(hot, key=lambda k: hot[k]["ms_per_step"])
     achieved = flops[dom] / (per[dom]["avg_us"] * 1e-6) / 1e12
     src_hash = kernel_source_hash()
     # the dominant kernel runs on the FP64 matrix cores when the plan uses the
-    # matrix-core variants (the FP64 MFMA and VALU peaks are both 78.6 TFLOP/s)
-    mfma = ("bwd=mfma" in pplan.describe()) if dom == "force_mm" else ("fwd=mfma" in pplan.describe())
+    # matrix-core variants (the FP64 MFMA and VALU peaks are both 78.6 TFLOP/s);
+    # reading the mesh is vector work, spreading to it runs on the matrix cores
+    mfma = {"force_mm": "bwd=mfma" in pplan.describe(), "sfac_mm": "fwd=mfma" in pplan.describe(),
+            "mesh_force": False, "mesh_sfac": True}[dom]
     roof = dict(bound="mfma" if mfma else "alu", achieved=round(achieved, 3), peak=FP64_PEAK_TFLOPS, unit="TFLOP/s",
                 frac=round(achieved / FP64_PEAK_TFLOPS, 4), traffic=traffic_from_profiles(dom, src_hash),
                 kernel=dom, flops_per_launch=flops[dom], avg_launch_us=round(per[dom]["avg_us"], 2),
@@ -191,8 +209,7 @@ def main():
     roof["isolated_executed_frac_vs_measured"] = (None if iso is None or not unit_peak else
                                                   round(executed[dom] / (iso * 1e-6) / 1e12 / unit_peak, 4))
     hot_total_us = sum(per[k]["avg_us"] for k in hot)
-    path_flops = 10.0 * nh * s.nm
-    path_exec = 12.0 * nh * s.nm
+    path_flops, path_exec = sum(flops.values()), sum(executed.values())
     extra = dict(
         hot_path=dict(kernels={k: dict(avg_us=round(per[k]["avg_us"], 2),
                                        algorithmic_frac=round(flops[k] / (per[k]["avg_us"] * 1e-6) / 1e12
@@ -203,7 +220,8 @@ def main():
                       ms_per_step_bracketed=round(ms_hot, 4),
                       step_frac_of_fp64_peak=round(path_flops / (ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, 4),
                       step_executed_frac_of_fp64_peak=round(path_exec / (ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, 4)),
-        flop_model="per (k in the half space, MM atom): forward 4 (folded minimal count), adjoint 6 (forces); "
+        flop_model="gridded sums: 16^3 mesh points per MM charge, 2 flops each spread and 4 read, plus the axis "
+                   "contractions; dense sums: per (k in the half space, MM charge) 4 forward and 6 adjoint, "
                    "executed 4 + 8",
         kernel_source_hash=src_hash, plan=pplan.describe())
 
@@ -303,7 +321,8 @@ def _fp64_peaks(dev, blocks=2048):
 
 def _isolated_us(cache, describe, kernel):
     """Standalone launch time (us) of the plan's hot-loop candidate from the autotune cache, or None."""
-    import re
+    if kernel not in ("force_mm", "sfac_mm"):  # the gridded sums have no tuned candidates
+        return None
     try:
         lines = open(cache).read().strip().splitlines()
     except OSError:
@@ -327,8 +346,8 @@ def _isolated_us(cache, describe, kernel):
 
 
 def _per_config(dev, no_autotune, steps=5):
-    """Every configuration against the algorithmic model (10 flops per (k, MM
-    atom) forward + adjoint, 4 forward only): c1, c2 as single frames through
+    """Every configuration against the algorithmic model of its plan
+    (:func:`recip_flops`; the plain path: 4 flops per (k, MM atom)): c1, c2 as single frames through
     autograd, c5 as one batched call of its 16 replicas (FP64 and the mixed-
     precision variants, with their deviation from FP64), and the plain forward
     path (one thread per k, sincos per term) on c1, c2, c3 and one c5 replica."""
@@ -358,6 +377,7 @@ def _per_config(dev, no_autotune, steps=5):
         plan = Plan(EwaldConfig(box=tuple(s.box), alpha=s.alpha, rcut=s.rcut, kmax=s.kmax, max_qm=s.nq, max_mm=s.nm))
         if not no_autotune:
             plan.autotune(s.nm)
+        fl = sum(recip_flops(plan.describe(), s.kmax, float(s.nm))[0].values())
         x = [torch.tensor(a, dtype=torch.float64, device=dev, requires_grad=True)
              for a in (s.qm_pos, s.Q, s.mu, s.theta, s.mm_pos, s.q)]
 
@@ -373,8 +393,8 @@ def _per_config(dev, no_autotune, steps=5):
         ob = plan.batch(desc, *xd)
         ms_g = timed(lambda: plan.batch(desc, *xd, out=ob), 4 * steps)
         out[f"c{cfg}"] = dict(n_mm=s.nm, n_kvec_half_space=nh, ms_per_frame_fwd_bwd=round(ms, 4),
-                              frames_per_s=round(1e3 / ms, 1), frac_of_fp64_peak=frac(10.0 * nh * s.nm, ms),
-                              graph_replay_ms=round(ms_g, 4), graph_replay_frac=frac(10.0 * nh * s.nm, ms_g))
+                              frames_per_s=round(1e3 / ms, 1), frac_of_fp64_peak=frac(fl, ms),
+                              graph_replay_ms=round(ms_g, 4), graph_replay_frac=frac(fl, ms_g))
         plan.close()
     # c5: 16 replicas of 100 000 MM charges, FP64 and the mixed-precision variants
     v = _batch_variants(dev, 5, 16, ("fp32_real", "fp32_recip", "fp32_all"), steps)
@@ -527,8 +547,6 @@ def _batch_variants(dev, cfg, nframes, variants, steps):
                                  device=dev)
     x = [cat("qm_pos"), cat("Q"), cat("mu"), cat("theta"), cat("mm_pos"), cat("q")]
     f0 = frames[0]
-    nh = n_half_space(f0.kmax)
-    fl = 10.0 * nh * float(moff[-1])
     out, ref = {}, None
     for prec in ("fp64",) + tuple(variants):
         plan = Plan(EwaldConfig(box=tuple(f0.box), alpha=f0.alpha, rcut=f0.rcut, kmax=f0.kmax, max_qm=int(qoff[-1]),
@@ -544,6 +562,7 @@ def _batch_variants(dev, cfg, nframes, variants, steps):
             plan.batch(desc, *x, out=o)
         torch.cuda.synchronize()
         ms = (time.perf_counter() - t0) * 1e3 / steps
+        fl = sum(recip_flops(plan.describe(), f0.kmax, float(moff[-1]), nframes)[0].values())
         r = dict(frames=nframes, total_mm=int(moff[-1]), ms_per_batch=round(ms, 3),
                  frames_per_s=round(nframes * 1e3 / ms, 1),
                  frac_of_fp64_peak=round(fl / (ms * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, 4), plan=plan.describe())

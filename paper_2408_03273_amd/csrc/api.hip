@@ -54,6 +54,11 @@ struct ewald_plan {
   Tuning t;
   Work w;
   int cap_qm, cap_mm, cap_frames, cap_slots, cap_kc, cap_cells;
+  // gridded reciprocal sums: mesh shape, whether its workspace is allocated,
+  // and the choice between it and the dense sums: -1 by size, 0 never, 1 always
+  Mesh mesh;
+  bool mesh_ok = false;
+  int mesh_mode = -1;
   std::vector<void*> allocs;
   std::string describe;
   // batched graph state
@@ -95,7 +100,9 @@ bool profiling(const ewald_plan* pl) {
 bool profiled_launch(const ewald_plan* pl, const char* name) {
   if (!profiling(pl)) return false;
   if (pl->p.flags & EWALD_PROFILE) return true;
-  return strncmp(name, "launch_force_mm(", 16) == 0 || strncmp(name, "launch_sfac_mm(", 15) == 0;
+  for (const char* hot : {"launch_force_mm(", "launch_sfac_mm(", "launch_mesh_force(", "launch_mesh_sfac("})
+    if (strncmp(name, hot, strlen(hot)) == 0) return true;
+  return false;
 }
 
 hipEvent_t pool_event(ewald_plan* pl) {
@@ -183,6 +190,42 @@ ewald_status_t alloc(ewald_plan* pl, T** ptr, size_t count) {
   return EWALD_OK;
 }
 
+// Workspace of the gridded reciprocal sums in doubles (per frame, per MM atom).
+size_t mesh_frame_doubles(const Mesh& m) {
+  const size_t q = (size_t)m.N[0] * m.N[1] * m.N[2], h = (size_t)m.N[0] * m.N[1] * m.C[2],
+               c = (size_t)m.N[0] * m.C[1] * m.C[2], t = (size_t)m.C[0] * m.C[1] * m.C[2];
+  return 2 * (q + h + c + t) + m.nbt + 1;
+}
+constexpr size_t kMeshAtomDoubles = 48 + 4 + 1 + 1;
+
+// Whether the gridded sums are the faster: with F frames and n MM atoms in all,
+// dense sums cost about 0.22 ps per (atom, k vector), gridded ones 2.2 ns per
+// atom, 22 ps per mesh point of each frame and some 70 us for the longer chain
+// of launches (from batches of 16 and single frames of 600 to 60 000 atoms at
+// kmax 8 to 32; e.g. 16 frames of 6000 atoms at kmax 24: 1551 us dense, 1007
+// gridded; at kmax 12: 467 and 524).
+bool mesh_pays(const Mesh& m, int KF, double n_frames, double atoms) {
+  const double points = (double)m.N[0] * m.N[1] * m.N[2];
+  return atoms * ((double)KF - 1e4) > 100.0 * points * n_frames + 3e8;
+}
+
+// Gridded or dense reciprocal sums for a call over these frames.  The mesh
+// needs the Ewald weights to fall off enough at the band edge in every frame's
+// box.
+bool use_mesh(const ewald_plan* pl, const FrameDev* frames, int n_frames) {
+  if (!pl->mesh_ok || pl->mesh_mode == 0) return false;
+  double atoms = 0.0;
+  for (int f = 0; f < n_frames; f++) {
+    for (int a = 0; a < 3; a++) {
+      const double x = M_PI * pl->mesh.m[a] / (pl->p.alpha * frames[f].box[a]);
+      if (!(x * x >= pl->mesh.damping[a])) return false;
+    }
+    atoms += frames[f].nm;
+  }
+  if (atoms == 0.0) return false;
+  return pl->mesh_mode == 1 || mesh_pays(pl->mesh, pl->g.KF, n_frames, atoms);
+}
+
 int fwd_kblocks(const ewald_plan* pl) { return fwd_col_groups(pl->g, pl->t); }
 
 // smallest forward block count per atom chunk over the kernel variants (sizes the partial-sum slots)
@@ -228,6 +271,64 @@ void free_plan(ewald_plan* pl) {
   pl->allocs.clear();
 }
 
+// Workspace and tables of the gridded sums; on failure everything taken here is given back.
+constexpr size_t kMeshMaxBytes = (size_t)32 << 30;
+
+ewald_status_t alloc_mesh(ewald_plan* pl) {
+  const Mesh& m = pl->mesh;
+  Work& w = pl->w;
+  const size_t cm = pl->cap_mm, cf = pl->cap_frames, held = pl->allocs.size();
+  const size_t q = (size_t)m.N[0] * m.N[1] * m.N[2], h = (size_t)m.N[0] * m.N[1] * m.C[2],
+               c = (size_t)m.N[0] * m.C[1] * m.C[2], t = (size_t)m.C[0] * m.C[1] * m.C[2];
+  std::vector<double> poly, fwd[3], bwd[3];
+  ewald_status_t st = EWALD_OK;
+  auto take = [&](auto** p, size_t n) {
+    if (st == EWALD_OK) st = alloc(pl, p, n);
+  };
+  auto upload = [&](double** p, const std::vector<double>& v) {
+    take(p, v.size());
+    if (st == EWALD_OK && hipMemcpy(*p, v.data(), v.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+      st = fail(EWALD_ERR_HIP, "hipMemcpy failed");
+  };
+  take(&w.mesh_cnt, cf * m.nbt);
+  take(&w.mesh_start, cf * (m.nbt + 1));
+  take(&w.mesh_slot, cm);
+  take(&w.mesh_taps, cm * 48);
+  take(&w.mesh_off, cm);
+  take(&w.mesh_cell, cm);
+  take(&w.mesh_q, cf * q);
+  take(&w.mesh_h, cf * h);
+  take(&w.mesh_g, cf * c);
+  take(&w.mesh_t, cf * t);
+  take(&w.mesh_bt, cf * t);
+  take(&w.mesh_bg, cf * c);
+  take(&w.mesh_bh, cf * h);
+  take(&w.mesh_v, cf * q);
+  if (pl->p.flags & EWALD_DETERMINISTIC) take(&w.mesh_perm, cm);
+  if (st == EWALD_OK) {
+    mesh_tables(m, poly, fwd, bwd);
+    upload(&w.mesh_poly, poly);
+    for (int a = 0; a < 3; a++) {
+      upload(&w.mesh_tab[a], fwd[a]);
+      upload(&w.mesh_btab[a], bwd[a]);
+    }
+  }
+  // the bin counts start from zero (and every call leaves them so); the
+  // padding of the weights on the real basis is never written
+  if (st == EWALD_OK && (hipMemset(w.mesh_cnt, 0, sizeof(int) * cf * m.nbt) != hipSuccess ||
+                         hipMemset(w.mesh_bt, 0, sizeof(double) * cf * t) != hipSuccess))
+    st = fail(EWALD_ERR_HIP, "hipMemset failed");
+  if (st != EWALD_OK) {
+    (void)hipGetLastError();
+    while (pl->allocs.size() > held) {
+      (void)hipFree(pl->allocs.back());
+      pl->allocs.pop_back();
+    }
+    w.mesh_perm = nullptr;
+  }
+  return st;
+}
+
 const char* precision_name(int p) {
   switch (p) {
     case EWALD_FP32_REAL: return "fp32-real";
@@ -238,7 +339,9 @@ const char* precision_name(int p) {
 }
 
 void set_describe(ewald_plan* pl) {
-  char buf[256];
+  char buf[320], mesh[48] = "";
+  if (pl->mesh_ok && pl->mesh_mode != 0)
+    snprintf(mesh, sizeof(mesh), " mesh=%dx%dx%d", pl->mesh.N[0], pl->mesh.N[1], pl->mesh.N[2]);
   static const char* bwd[] = {"",           "valu-horner-1", "valu-horner-2", "mfma-fold-16",
                               "mfma-fold-32", "mfma-fold-ws",  "mfma-fold-eyl"};
   char fwd[64];
@@ -246,10 +349,10 @@ void set_describe(ewald_plan* pl) {
     snprintf(fwd, sizeof(fwd), "mfma-fold ct=%d nt=%d xcd=%d", pl->t.fwd_ct, pl->g.NT, pl->t.fwd_xcd);
   else
     snprintf(fwd, sizeof(fwd), "valu zc=%d nzp=%d", pl->g.Zc, pl->g.NZP);
-  snprintf(buf, sizeof(buf), "fwd=%s blocks~%d bwd=%s%s kc=%s kgrid=%dx%dx%d precision=%s", fwd, pl->t.fwd_target,
+  snprintf(buf, sizeof(buf), "fwd=%s blocks~%d bwd=%s%s kc=%s kgrid=%dx%dx%d precision=%s%s", fwd, pl->t.fwd_target,
            bwd[pl->t.bwd_ilp], pl->t.bwd_ilp == 6 ? (pl->t.bwd_xcd ? " xcd=1" : " xcd=0") : "",
            pl->t.kc > 0 ? std::to_string(pl->t.kc).c_str() : "auto", pl->g.NX, pl->g.NY, pl->g.NZ,
-           precision_name(pl->p.precision));
+           precision_name(pl->p.precision), mesh);
   pl->describe = buf;
 }
 
@@ -433,6 +536,7 @@ struct Seq {
   int fp32;
   int qmqm;
   int cells;  // real space over the cell list
+  int mesh = 0;  // reciprocal sums over the MM atoms on the mesh
   int mm_groups = 0;  // MM side of real space: 0 per pair, else site groups of the per-atom kernel
 };
 
@@ -471,7 +575,10 @@ ewald_status_t seq_forward_tail(const Seq& q, const double* Q, const double* mu,
                                 double* site, int with_adjoint = 0, int early = 0, int finalize = 1) {
   ewald_plan* pl = q.pl;
   const int mode = with_adjoint ? 2 : 0;
-  LCHK(launch_reduce_smm(pl->g, pl->t, q.fa, q.plain, smm, smm_stride, pl->w, q.s));
+  if (q.mesh)
+    LCHK(launch_mesh_smm(pl->mesh, pl->g, q.fa, smm, smm_stride, pl->w, q.s));
+  else
+    LCHK(launch_reduce_smm(pl->g, pl->t, q.fa, q.plain, smm, smm_stride, pl->w, q.s));
   LCHK(launch_project_qm(pl->g, q.fa, q.max_nq, q.total_nq, smm, smm_stride, Q, mu, theta, mode, q.qmqm, pl->w, q.s));
   if (!early) {  // early: real space and QM-QM were launched before the reciprocal work
     if (q.cells)
@@ -511,7 +618,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
   ewald_plan* pl = q.pl;
   Work& w = pl->w;
   const Grid& g = pl->g;
-  const int tables = mm_tables_for(pl);
+  const int tables = q.mesh ? 0 : mm_tables_for(pl);
   // positions, charge sums, cleared accumulators, unit effective moments
   ewald_status_t st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, tables, 1, PREP_POS);
   if (st != EWALD_OK) return st;
@@ -551,7 +658,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
       // adjoint hot loop follows as soon as the MM tables are ready
       LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm,
                        pl->cap_mm, tables, 1, PREP_QM_TAB));
-      LCHK(launch_sfac_qm(g, q.fa, q.max_nq, Q, mu, theta, w.qeff, nullptr, 1, w, q.s));
+      LCHK(launch_sfac_qm(g, q.fa, q.max_nq, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, w, q.s));
       HIPCHK(hipEventRecord(pl->ev_qside, q.s));
     }
   }
@@ -560,14 +667,20 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
   // would hold the forward back (the adjoint takes the GPU meanwhile), so
   // they go to the second stream, after real space
   const bool qq_first = q.fa.n_frames == 1;
-  LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm, pl->cap_mm,
-                   tables, 1, PREP_MM_TAB));
+  if (q.mesh)
+    LCHK(launch_mesh_sort(pl->mesh, q.fa, q.max_nm, pl->cap_mm, w, q.s));
+  else
+    LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm, pl->cap_mm,
+                     tables, 1, PREP_MM_TAB));
   HIPCHK(hipEventRecord(pl->ev_mtab, q.s));
   if (qq_first && q.qmqm && q.max_nq > 0) LCHK(launch_qmqm(g, q.fa, q.max_nq, pl->cap_qm, Q, mu, theta, w, q.s));
   // caller stream: the forward hot loop (with many frames after the QM side,
   // whose structure factors the adjoint needs: a forward grid beside them
   // would starve them and the adjoint would start long after the forward)
-  LCHK(launch_sfac_mm(g, pl->t, q.fa, q.max_nm, pl->cap_mm, w, q.s));
+  if (q.mesh)
+    LCHK(launch_mesh_sfac(pl->mesh, q.fa, w, q.s));
+  else
+    LCHK(launch_sfac_mm(g, pl->t, q.fa, q.max_nm, pl->cap_mm, w, q.s));
   {
     Seq qa = q;
     qa.s = aux;
@@ -578,7 +691,10 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
       // and MM-side adjoint in one pass), which runs beside the projection on
       // the caller stream and is needed only by the final epilogue
       HIPCHK(hipStreamWaitEvent(q.s, pl->ev_mtab, 0));
-      LCHK(launch_force_mm(g, pl->t, q.fa, q.max_nm, pl->cap_mm, w, q.s));
+      if (q.mesh)
+        LCHK(launch_mesh_force(pl->mesh, g, q.fa, q.max_nm, w, q.s));
+      else
+        LCHK(launch_force_mm(g, pl->t, q.fa, q.max_nm, pl->cap_mm, w, q.s));
       if (q.cells) {
         LCHK(launch_real_cells(g, q.fa, q.max_nq, pl->cap_qm, pl->cap_mm, 0, q.fp32, w, q.s));
         LCHK(launch_real_cells(g, q.fa, q.max_nq, pl->cap_qm, pl->cap_mm, 1, q.fp32, w, q.s));
@@ -710,6 +826,13 @@ ewald_status_t ewald_setup(const ewald_params_t* params, ewald_plan** plan) {
     pl->t.bwd_ilp = 6;
     if (!fp32r_ct_ok(pl->g, pl->t.fwd_ct)) pl->t.fwd_ct = 1;
   }
+  // MPEWALD_MESH = 0|1: never | wherever its workspace fits the gridded
+  // reciprocal sums; without it, naming a dense kernel or tile above chooses
+  // the dense sums
+  for (const char* e : {"MPEWALD_FWD", "MPEWALD_BWD", "MPEWALD_FWD_CT", "MPEWALD_FWD_PF", "MPEWALD_FWD_TARGET",
+                        "MPEWALD_FWD_XCD", "MPEWALD_BWD_XCD", "MPEWALD_KC", "MPEWALD_BATCH_TARGET"})
+    if (getenv(e)) pl->mesh_mode = 0;
+  if (const char* e = getenv("MPEWALD_MESH")) pl->mesh_mode = atoi(e) ? 1 : 0;
   if (const char* e = getenv("MPEWALD_FWD_TARGET")) {
     const int v = atoi(e);
     if (v >= 64 && v <= 65536) pl->t.fwd_target = v;
@@ -769,7 +892,7 @@ ewald_status_t ewald_setup(const ewald_params_t* params, ewald_plan** plan) {
     const size_t nb_pos = (std::max(cm, cq) + 255) / 256;
     A(w.det_frame, cf * nb_pos * 3);
     A(w.det_eff, cf * ((cq + 255) / 256));
-    A(w.det_smm, cf * (((size_t)g.KF + 255) / 256) * 2);
+    A(w.det_qqlr, cf * (((size_t)g.NCOL * (g.mz + 1) + 63) / 64));
     A(w.det_proj, cq * kDetPc * 26);
     A(w.det_real, cq * kDetChunks * 13);
     A(w.det_qq, cq);
@@ -778,6 +901,16 @@ ewald_status_t ewald_setup(const ewald_params_t* params, ewald_plan** plan) {
     A(w.mm_xy32, cm * g.NXY);
     A(w.mm_ztab32, cm * g.ZKP);
     A(w.wfrag32, cf * (size_t)g.NG * g.NK2 * 256);
+  }
+  // Workspace of the gridded sums where the plan's capacity can use them (not
+  // for the plain and FP32 reciprocal paths), up to kMeshMaxBytes; a plan
+  // without it keeps the dense sums.
+  if (!(p.flags & EWALD_PLAIN) && !pl->t.fp32r && pl->mesh_mode != 0 && mesh_shape(g, p.box, pl->mesh)) {
+    const Mesh& m = pl->mesh;
+    const bool wanted = pl->mesh_mode == 1 || mesh_pays(m, g.KF, 1.0, pl->cap_mm);
+    const size_t doubles = cf * mesh_frame_doubles(m) + cm * kMeshAtomDoubles;
+    pl->mesh_ok = wanted && doubles * 8 <= kMeshMaxBytes && alloc_mesh(pl) == EWALD_OK;
+    g_last_error.clear();
   }
 #undef A
   const double one = 1.0;
@@ -858,27 +991,35 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
   q.fa.n_frames = 1;
   q.cells = assign_cells(plan, &q.fa.f0, 1) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
+  q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
   if (ctx) plan->stale_ctx.erase(ctx);
   if (ctx && !q.plain) {
-    plan->t.kc = choose_kc(plan, n_mm);
+    plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
     CtxView cv = ctx_view(plan->g, ctx, n_qm, n_mm);
     st = seq_fwd_bwd(q, plan->serial ? s : plan->aux, plan->serial ? s : plan->aux2, qm_xyz, Q, mu, theta, mm_xyz, mm_q, cv.smm, plan->g.KF, energy, phi, efield,
                      efgrad, cv.site, cv.gq, cv.gQ, cv.gmu, cv.gth, cv.gm, cv.gmq);
     plan->t = saved;
     return st;
   }
-  st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, q.plain ? 0 : mm_tables_for(plan), 0);
+  st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, q.plain || q.mesh ? 0 : mm_tables_for(plan), 0);
+  if (st == EWALD_OK && q.mesh) {
+    const hipError_t e = launch_mesh_sort(plan->mesh, q.fa, n_mm, plan->cap_mm, plan->w, s);
+    if (e != hipSuccess) st = fail(EWALD_ERR_HIP, "mesh_sort launch: %s", hipGetErrorString(e));
+  }
   if (st == EWALD_OK) {
     hipError_t e;
     {
       ProfScope ps(plan, "launch_sfac_qm", s);
-      e = launch_sfac_qm(plan->g, q.fa, n_qm, Q, mu, theta, plan->w.qeff, nullptr, 0, plan->w, s);
+      e = launch_sfac_qm(plan->g, q.fa, n_qm, Q, mu, theta, plan->w.qeff, 0, plan->w, s);
     }
     if (e != hipSuccess) st = fail(EWALD_ERR_HIP, "sfac_qm launch: %s", hipGetErrorString(e));
   }
   if (st == EWALD_OK) {
     hipError_t e;
-    if (q.plain) {
+    if (q.mesh) {
+      ProfScope ps(plan, "launch_mesh_sfac(", s);
+      e = launch_mesh_sfac(plan->mesh, q.fa, plan->w, s);
+    } else if (q.plain) {
       ProfScope ps(plan, "launch_sfac_mm_plain", s);
       e = launch_sfac_mm_plain(plan->g, q.fa, plan->cap_mm, plan->w, s);
     } else {
@@ -923,10 +1064,11 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   q.max_nq = q.total_nq = n_qm;
   q.max_nm = q.total_nm = n_mm;
   Tuning saved = plan->t;
-  plan->t.kc = choose_kc(plan, n_mm);
   q.fa.frames = nullptr;
   q.fa.f0 = make_frame(plan->p.box, n_qm, n_mm, 0, 0, 0, plan->p.rcut);
   q.fa.n_frames = 1;
+  q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
+  plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
   q.cells = assign_cells(plan, &q.fa.f0, 1) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
   CtxView cv = ctx_view(plan->g, (void*)ctx, n_qm, n_mm);
@@ -957,14 +1099,19 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
     }                                                                                                  \
   } while (0)
   // the matrix-core backward kernel reads the MM phase tables in its epilogue
-  st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, plan->t.bwd_ilp >= 3 ? 1 : 0, 0);
+  st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, !q.mesh && plan->t.bwd_ilp >= 3 ? 1 : 0, 0);
   if (st != EWALD_OK) {
     plan->t = saved;
     return st;
   }
   STEP(launch_eff_moments(q.fa, n_qm, Q, mu, theta, gE, g_phi, g_efield, g_efgrad, w, s));
-  STEP(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, gE, 1, w, s));
-  STEP(launch_force_mm(g, plan->t, q.fa, n_mm, plan->cap_mm, w, s));
+  STEP(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, w, s));
+  if (q.mesh) {
+    STEP(launch_mesh_sort(plan->mesh, q.fa, n_mm, plan->cap_mm, w, s));
+    STEP(launch_mesh_force(plan->mesh, g, q.fa, n_mm, w, s));
+  } else {
+    STEP(launch_force_mm(g, plan->t, q.fa, n_mm, plan->cap_mm, w, s));
+  }
   if (q.cells) {
     STEP(launch_zero(w.rpart, (size_t)plan->cap_mm * 4, s));
     STEP(launch_real_cells(g, q.fa, n_qm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s));
@@ -995,15 +1142,16 @@ namespace {
 // 64 frames at kmax 20, 1.1 MB of weights, are 1% faster on two streams; 16
 // frames at kmax 32, 4.4 MB, 4-5% faster on one, in FP64 and with the FP32
 // reciprocal kernels).
-bool batch_one_stream(const ewald_plan* pl) {
+bool batch_one_stream(const ewald_plan* pl, int mesh) {
   if (pl->batch_serial >= 0) return pl->batch_serial != 0;
+  if (mesh) return true;
   if (pl->t.bwd_ilp < 3) return false;
   const size_t weights = (size_t)pl->g.NG * pl->g.NK2 * 256 * sizeof(double);
   return weights > (size_t)2 << 20;
 }
 
-ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int cells, int mm_groups, int max_nq,
-                             int max_nm,
+ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int cells, int mesh, int mm_groups,
+                             int max_nq, int max_nm,
                              int total_nq, int total_nm, const double* qm_xyz, const double* Q, const double* mu,
                              const double* theta, const double* mm_xyz, const double* mm_q, int mode, double* energy,
                              double* phi, double* efield, double* efgrad, double* g_qm_xyz, double* g_Q,
@@ -1023,18 +1171,24 @@ ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int 
   q.fa.n_frames = n_frames;
   memset(&q.fa.f0, 0, sizeof(q.fa.f0));
   q.cells = cells;
+  q.mesh = mesh;
   q.mm_groups = mm_groups;
   Work& w = plan->w;
   const Grid& g = plan->g;
   if (mode == EWALD_FWD_BWD) {
-    const bool one = plan->serial || batch_one_stream(plan);
+    const bool one = plan->serial || batch_one_stream(plan, mesh);
     return seq_fwd_bwd(q, one ? s : plan->gaux, one ? s : plan->gaux2, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w.smm,
                        g.KF, energy, phi, efield, efgrad, w.site, g_qm_xyz, g_Q, g_mu, g_theta, g_mm_xyz, g_mm_q);
   }
-  ewald_status_t st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, mm_tables_for(pl), 0);
+  ewald_status_t st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, mesh ? 0 : mm_tables_for(pl), 0);
   if (st != EWALD_OK) return st;
-  LCHK(launch_sfac_qm(g, q.fa, max_nq, Q, mu, theta, w.qeff, nullptr, 0, w, s));
-  LCHK(launch_sfac_mm(g, plan->t, q.fa, max_nm, plan->cap_mm, w, s));
+  LCHK(launch_sfac_qm(g, q.fa, max_nq, Q, mu, theta, w.qeff, 0, w, s));
+  if (mesh) {
+    LCHK(launch_mesh_sort(pl->mesh, q.fa, max_nm, pl->cap_mm, w, s));
+    LCHK(launch_mesh_sfac(pl->mesh, q.fa, w, s));
+  } else {
+    LCHK(launch_sfac_mm(g, plan->t, q.fa, max_nm, plan->cap_mm, w, s));
+  }
   return seq_forward_tail(q, Q, mu, theta, w.smm, g.KF, energy, phi, efield, efgrad, w.site);
 }
 
@@ -1088,7 +1242,6 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
   Tuning use = plan->t;
   plan->t.a_chunk = saved.a_chunk;
   use.a_chunk = choose_a_chunk(plan, nms);
-  use.kc = choose_kc(plan, total_nm);
   // frame descriptors with partial-sum slots, largest frames first: the grid
   // dimension that runs over frames is dispatched in order, so the longest
   // work starts first and the small frames fill in at the end
@@ -1106,6 +1259,8 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
     slot += (fr.n_mm + use.a_chunk - 1) / use.a_chunk;
   }
   use.fwd_units = n_frames > 1 ? slot : 0;
+  const int mesh = use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
+  use.kc = mesh ? 1 : choose_kc(plan, total_nm);
   const int cells = assign_cells(plan, hf.data(), n_frames) ? 1 : 0;
   const int mm_groups = real_mm_groups(plan, hf.data(), n_frames);
   // graph key: frames, pointers, mode, stream, tiles
@@ -1116,6 +1271,7 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
   for (auto p : ptrs) key_push(key, p);
   key_push(key, mode);
   key_push(key, use);
+  key_push(key, mesh);
   hipStream_t s = (hipStream_t)stream;
   if (!plan->gstream) {
     HIPCHK(hipStreamCreateWithFlags(&plan->gstream, hipStreamNonBlocking));
@@ -1137,7 +1293,7 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
     HIPCHK(hipStreamBeginCapture(plan->gstream, hipStreamCaptureModeThreadLocal));
     plan->capturing = true;
     // QM accumulators are indexed by packed row, so clear every row up to the last one used
-    st = enqueue_batch(plan, plan->gstream, n_frames, cells, mm_groups, max_nq, max_nm, (int)end_q, (int)total_nm,
+    st = enqueue_batch(plan, plan->gstream, n_frames, cells, mesh, mm_groups, max_nq, max_nm, (int)end_q, (int)total_nm,
                        qm_xyz, Q, mu, theta, mm_xyz, mm_q, mode, energy, phi, efield, efgrad, g_qm_xyz, g_Q, g_mu,
                        g_theta, g_mm_xyz, g_mm_q);
     hipError_t ce = hipStreamEndCapture(plan->gstream, &graph);
@@ -1246,11 +1402,9 @@ extern "C" ewald_status_t ewald_moments_update(ewald_plan* plan, const void* ctx
   plan->stale_ctx.insert(ctx);
   st = seq_begin(q, qm_xyz, Q, mu, theta, nullptr, nullptr, 0, 1);
   if (st != EWALD_OK) return st;
-  LCHK(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, nullptr, 0, w, s));
+  LCHK(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, 0, w, s));
   if (q.qmqm && n_qm > 0) {
-    Tuning tq = plan->t;
-    tq.a_chunk = 64;  // no MM atoms: no partial-sum slots to read
-    LCHK(launch_reduce_smm(g, tq, q.fa, 0, w.smm, g.KF, w, s));
+    // (the projection's QM-MM sums, taken from whatever S_MM is there, are not used)
     LCHK(launch_project_qm(g, q.fa, n_qm, n_qm, w.smm, g.KF, Q, mu, theta, 1, 1, w, s));
     LCHK(launch_qmqm(g, q.fa, n_qm, plan->cap_qm, Q, mu, theta, w, s));
   }
@@ -1546,6 +1700,8 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
   hipEvent_t e0 = nullptr, e1 = nullptr;
   ewald_status_t st = EWALD_OK;
   const Tuning saved = plan->t;
+  const int saved_mesh = plan->mesh_mode;
+  plan->mesh_mode = 0;  // the tiles are those of the dense sums
   double best_f = 1e30, best_b = 1e30;
   Tuning best = saved;
   std::string report;
@@ -1587,7 +1743,7 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
     q.fa.n_frames = 1;
     st = seq_begin(q, dqp, dQ, dmu, dth, dm, dq, 2, 1);
     if (st != EWALD_OK) goto done;
-    TCHK(launch_sfac_qm(plan->g, q.fa, nq, dQ, dmu, dth, plan->w.qeff, nullptr, 1, plan->w, s));
+    TCHK(launch_sfac_qm(plan->g, q.fa, nq, dQ, dmu, dth, plan->w.qeff, 2, plan->w, s));
     auto time_it = [&](auto&& launch) -> double {
       hipError_t e = launch();  // warm-up
       if (e != hipSuccess) return -1.0;
@@ -1757,6 +1913,7 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
   }
 done:
 #undef TCHK
+  plan->mesh_mode = saved_mesh;
   plan->t = st == EWALD_OK ? best : saved;
   plan->t.a_chunk = 0;
   if (s) (void)hipStreamSynchronize(s);

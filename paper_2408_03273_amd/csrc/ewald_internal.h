@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace mpe {
 
 // Per-frame description as the kernels see it.
@@ -77,12 +79,23 @@ enum QmSlot {
 enum FrameSlot {
   FA_QTOT_MM = 0,
   FA_QTOT_QM = 1,
-  FA_E_QMMM_LR = 2,
   FA_E_QQ_LR = 3,
   FA_E_QQ_SR = 4,   // real space + self + background
   FA_QTOT_EFF = 5,  // sum of effective charges (backward)
   FA_COUNT = 8
 };
+
+// Shape of the mesh of the gridded reciprocal sums (identical for every frame
+// of a plan; axis 0 = x).
+struct Mesh {
+  int N[3];   // mesh points per axis
+  int nb[3];  // bins of 4 mesh cells per axis
+  int nbt;    // bins
+  int C[3];   // real basis functions per axis, 2 m + 1 padded to a multiple of 16
+  int m[3];   // highest wave number
+  double damping[3];  // smallest (pi m / (alpha L))^2 the mesh is accurate for
+};
+static constexpr int kMeshPoly = 20;  // coefficients of a tap's polynomial
 
 // Device buffers of a plan (all sized for the plan capacities).
 struct Work {
@@ -123,11 +136,30 @@ struct Work {
   float2* mm_xy32;    // [cap_mm][NXY]
   float* mm_ztab32;   // [cap_mm][ZKP]
   float* wfrag32;     // [cap_frames][NG][NK2][4][64]
+  // gridded reciprocal sums only (null otherwise); "sorted": by frame, then bin
+  int* mesh_cnt;       // [cap_frames][nbt]      atoms per bin (zero between calls)
+  int* mesh_start;     // [cap_frames][nbt + 1]  first sorted atom of each bin
+  int2* mesh_slot;     // [cap_mm]               bin and rank of each atom
+  int* mesh_perm;      // [cap_mm]               deterministic plans: atoms listed by bin
+  double* mesh_taps;   // [cap_mm][3][16]        kernel values (x: times q), sorted by bin
+  double4* mesh_off;   // [cap_mm]               offsets in the mesh cell (2t - 1), sorted
+  int2* mesh_cell;     // [cap_mm]               mesh cell (10 bits per axis) and row, sorted
+  double* mesh_poly;   // [8][kMeshPoly]         tap polynomials
+  double* mesh_tab[3]; // basis tables of the forward and adjoint contractions, in fragment order
+  double* mesh_btab[3];
+  double* mesh_q;      // [cap_frames][N0][N1][N2]  spread charges; then their contractions over z, y, x:
+  double* mesh_h;      // [cap_frames][N0][N1][C2]
+  double* mesh_g;      // [cap_frames][N0][C1][C2]
+  double* mesh_t;      // [cap_frames][C0][C1][C2]
+  double* mesh_bt;     // adjoint weights on the real basis, and their contractions over x, y, z
+  double* mesh_bg;
+  double* mesh_bh;
+  double* mesh_v;
   // deterministic mode only (null otherwise): per-block partial sums, added
   // in a fixed order by k_det_reduce instead of floating-point atomics
   double* det_frame;  // [cap_frames][ceil(max(cap_mm, cap_qm) / 256)][3] charge sums of k_prep_pos
   double* det_eff;    // [cap_frames][ceil(cap_qm / 256)]              effective charge sums
-  double* det_smm;    // [cap_frames][ceil(KF / 256)][2]                long-range energies
+  double* det_qqlr;   // [cap_frames][ceil(NCOL (mz + 1) / 64)]         long-range QM-QM energies
   double* det_proj;   // [cap_qm][kDetPc][26]                          QM-site projection sums
   double* det_real;   // [cap_qm][kDetChunks][13]                      real-space QM-side sums
   double* det_qq;     // [cap_qm]                                       QM-QM site energies
@@ -226,11 +258,22 @@ hipError_t launch_prep(const Grid& g, const FrameArg& fa, int max_nq, int max_nm
                        const double* Q, const double* mu, const double* theta, const double* mm_xyz,
                        const double* mm_q, Work& w, hipStream_t s, int cap_qm, int cap_mm, int mm_tables,
                        int unit_eff, int parts = PREP_ALL);
+// with_w: 0 no adjoint weights, 1 in k order, 2 also in matrix-core operand order
 hipError_t launch_sfac_qm(const Grid& g, const FrameArg& fa, int max_nq, const double* Q, const double* mu,
-                          const double* theta, const double* qeff, const double* gE, int with_w, Work& w,
-                          hipStream_t s);
+                          const double* theta, const double* qeff, int with_w, Work& w, hipStream_t s);
 hipError_t launch_sfac_mm(const Grid& g, const Tuning& t, const FrameArg& fa, int max_nm, int cap_mm, Work& w,
                           hipStream_t s);
+// gridded reciprocal sums (mesh.hip): atoms sorted into bins with their kernel
+// values; structure factor on the real basis; S_MM in k order from it;
+// potential and gradient of the adjoint weights w.wk at the atoms into fpart
+bool mesh_shape(const Grid& g, const double box[3], Mesh& m);
+void mesh_tables(const Mesh& m, std::vector<double>& poly, std::vector<double> (&fwd)[3],
+                 std::vector<double> (&bwd)[3]);
+hipError_t launch_mesh_sort(const Mesh& m, const FrameArg& fa, int max_nm, int cap_mm, Work& w, hipStream_t s);
+hipError_t launch_mesh_sfac(const Mesh& m, const FrameArg& fa, Work& w, hipStream_t s);
+hipError_t launch_mesh_smm(const Mesh& m, const Grid& g, const FrameArg& fa, double2* smm, size_t smm_stride, Work& w,
+                           hipStream_t s);
+hipError_t launch_mesh_force(const Mesh& m, const Grid& g, const FrameArg& fa, int max_nm, Work& w, hipStream_t s);
 hipError_t launch_sfac_mm_plain(const Grid& g, const FrameArg& fa, int cap_mm, Work& w, hipStream_t s);
 hipError_t launch_reduce_smm(const Grid& g, const Tuning& t, const FrameArg& fa, int plain, double2* smm_out,
                              size_t smm_frame_stride, Work& w, hipStream_t s);

@@ -418,6 +418,8 @@ static void launch_tab(const Grid& g, const FrameArg& fa, int qm_side, int with_
 //   sum_nz W(c,nz) e^{-i nz kz0 z} = W(c,0) + sum_p [Ap cos(p kz0 z) - i Am sin(p kz0 z)]
 //   sum_nz nz W(c,nz) e^{-i nz kz0 z} = sum_p p [Am cos(p kz0 z) - i Ap sin(p kz0 z)].
 // Each thread owns one column and one p and evaluates both k = (nx, ny, +p) and (nx, ny, -p).
+// The reciprocal part of the order-2 truncated QM-QM image energy,
+// (4 pi/V) g (|A|^2 + 2 Re A*B + 2 Re A*C + |B|^2), is summed along the way.
 DEV void qm_terms(double (&v)[8], double2 e, double Qj, double kmu, double kthk) {
   v[0] += Qj * e.x;
   v[1] += Qj * e.y;
@@ -432,7 +434,8 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
                                                  const double* __restrict__ qeff, const double2* __restrict__ qtab,
                                                  int with_w, double2* __restrict__ sabc, double2* __restrict__ wk,
                                                  double* __restrict__ kw, double* __restrict__ wfrag,
-                                                 double2* __restrict__ wk0) {
+                                                 double2* __restrict__ wk0, double* __restrict__ facc,
+                                                 double* __restrict__ det) {
   const int f = blockIdx.y;
   const FrameDev fr = get_frame(fa, f);
   const int lane = threadIdx.x & 63;
@@ -480,7 +483,9 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
       red[wave - 1][8 + u][lane] = vm[u];
     }
   __syncthreads();
-  if (wave != 0 || t >= g.NCOL * NP) return;
+  if (wave != 0) return;
+  const bool live = t < g.NCOL * NP;
+  double eqq = 0.0;
   for (int u = 0; u < 8; u++) {
     vp[u] += red[0][u][lane] + red[1][u][lane] + red[2][u][lane];
     vm[u] += red[0][8 + u][lane] + red[1][8 + u][lane] + red[2][8 + u][lane];
@@ -492,22 +497,32 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
     const int nz = sg ? -p : p;
     const double* v = sg ? vm : vp;
     const int k = col * g.NZ + g.mz + nz;
-    double2* o = sabc + ((size_t)f * g.KF + k) * 3;
-    o[0] = make_double2(v[0], v[1]);
-    o[1] = make_double2(v[2], v[3]);
-    o[2] = make_double2(v[4], v[5]);
     double wgt = 0.0;
     if (in_half_space(nx, ny, nz)) {
       const double k2 = kx * kx + ky * ky + kz * kz;
       wgt = 8.0 * kPi / V * exp(-k2 / (4.0 * g.alpha * g.alpha)) / k2;
     }
-    kw[(size_t)f * g.KF + k] = wgt;
-    if (with_w) {
-      W[sg] = make_double2(wgt * v[6], wgt * v[7]);
-      wk[(size_t)f * g.KF + k] = W[sg];
+    if (with_w) W[sg] = make_double2(wgt * v[6], wgt * v[7]);
+    if (live) {
+      if (wgt != 0.0)
+        eqq += 0.5 * wgt * ((v[0] * v[0] + v[1] * v[1]) + 2.0 * (v[0] * v[2] + v[1] * v[3]) +
+                            2.0 * (v[0] * v[4] + v[1] * v[5]) + (v[2] * v[2] + v[3] * v[3]));
+      double2* o = sabc + ((size_t)f * g.KF + k) * 3;
+      o[0] = make_double2(v[0], v[1]);
+      o[1] = make_double2(v[2], v[3]);
+      o[2] = make_double2(v[4], v[5]);
+      kw[(size_t)f * g.KF + k] = wgt;
+      if (with_w) wk[(size_t)f * g.KF + k] = W[sg];
     }
   }
-  if (with_w && wfrag) {
+  eqq = wave_sum(eqq);
+  if (lane == 0) {
+    if (det)
+      det[(size_t)f * gridDim.x + blockIdx.x] = eqq;
+    else
+      atomicAdd(&facc[f * FA_COUNT + FA_E_QQ_LR], eqq);
+  }
+  if (live && with_w && wfrag) {
     if (p == 0) {
       wk0[(size_t)f * g.NG * 16 + col] = W[0];
     } else {
@@ -536,15 +551,19 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
 }
 
 hipError_t launch_sfac_qm(const Grid& g, const FrameArg& fa, int max_nq, const double* Q, const double* mu,
-                          const double* theta, const double* qeff, const double* gE, int with_w, Work& w,
-                          hipStream_t s) {
+                          const double* theta, const double* qeff, int with_w, Work& w, hipStream_t s) {
   (void)max_nq;
-  (void)gE;
   dim3 grid((g.NCOL * (g.mz + 1) + 63) / 64, fa.n_frames);
+  // with_w: 1 the adjoint weights in k order (gridded adjoint), 2 also in matrix-core order
   hipLaunchKernelGGL(k_sfac_qm, grid, dim3(256), 0, s, g, fa, Q, mu, theta, qeff, w.qm_tab, with_w, w.sabc, w.wk,
-                     w.kw, w.wfrag, w.wk0);
-  if (with_w && w.wfrag32) return launch_wfrag32(g, fa, w, s);
-  return hipGetLastError();
+                     w.kw, with_w == 2 ? w.wfrag : (double*)nullptr, w.wk0, w.facc, w.det_qqlr);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (w.det_qqlr) {
+    e = launch_det_reduce(fa, 0, 1, w.det_qqlr, (int)grid.x, 1, det_map({FA_E_QQ_LR}), w.facc, FA_COUNT, s);
+    if (e != hipSuccess) return e;
+  }
+  return with_w == 2 && w.wfrag32 ? launch_wfrag32(g, fa, w, s) : hipSuccess;
 }
 
 // v_mfma_f64_16x16x4f64: D(16x16) += A(16x4) B(4x16).  A[i][k] sits in lane
@@ -1043,94 +1062,51 @@ hipError_t launch_sfac_mm_plain(const Grid& g, const FrameArg& fa, int cap_mm, W
   return hipGetLastError();
 }
 
-// Sum the partial structure factors, store S_MM in k order, and accumulate
-// the reciprocal energies (8 pi/V) g Re[S_QM conj S_MM] and the order-2
-// truncated QM-QM term (4 pi/V) g (|A|^2 + 2Re A*B + 2Re A*C + |B|^2).
-// Partial sums are in k order (kmajor, matrix-core forward) or nz-major
+// Sum the partial structure factors over the atom chunks and store S_MM in k
+// order.  Partial sums are in k order (kmajor, matrix-core forward) or nz-major
 // (VALU and plain forward).
-// One item: the 256 reciprocal vectors of block kb (of nkb) of frame f; red
-// holds 8 doubles of LDS.
-DEV void reduce_smm_item(const Grid& g, const FrameDev& fr, int f, int kb, int nkb, int a_chunk, int plain,
-                         int kmajor, const double2* __restrict__ spart, const double2* __restrict__ sabc,
-                         const double* __restrict__ kw, double2* __restrict__ smm, size_t smm_stride,
-                         double* __restrict__ facc, double* __restrict__ det, double* red) {
-  const int k = kb * 256 + threadIdx.x;
-  double v[2] = {0.0, 0.0};
-  if (k < g.KF) {
-    const int col = k / g.NZ, iz = k - col * g.NZ;
-    const int nslots = plain ? 1 : (fr.nm + a_chunk - 1) / a_chunk;
-    const size_t idx = kmajor ? (size_t)k : (size_t)iz * g.NCOL + col;
-    // eight partials in flight per round trip (a load-add chain per slot left
-    // the kernel latency bound); the slots are still summed in order
-    const size_t sstride = (size_t)g.NZP * g.NCOL;
-    const double2* __restrict__ pp = spart + (size_t)fr.slot_base * sstride + idx;
-    double sr = 0.0, si = 0.0;
-    int sl = 0;
-    for (; sl + 8 <= nslots; sl += 8) {
-      double2 p[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) p[u] = pp[(size_t)(sl + u) * sstride];
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        sr += p[u].x;
-        si += p[u].y;
-      }
-    }
-    for (; sl < nslots; sl++) {
-      const double2 p = pp[(size_t)sl * sstride];
-      sr += p.x;
-      si += p.y;
-    }
-    if (plain && fr.nm == 0) sr = si = 0.0;
-    smm[(size_t)f * smm_stride + k] = make_double2(sr, si);
-    const double wgt = kw[(size_t)f * g.KF + k];
-    if (wgt != 0.0) {
-      const double2* abc = sabc + ((size_t)f * g.KF + k) * 3;
-      const double2 A = abc[0], B = abc[1], C = abc[2];
-      const double sqr = A.x + B.x + C.x, sqi = A.y + B.y + C.y;
-      v[0] = wgt * (sqr * sr + sqi * si);
-      const double F = (A.x * A.x + A.y * A.y) + 2.0 * (A.x * B.x + A.y * B.y) + 2.0 * (A.x * C.x + A.y * C.y) +
-                       (B.x * B.x + B.y * B.y);
-      v[1] = 0.5 * wgt * F;
-    }
-  }
-  double tot[2];
-  block_sum256_lds<2>(v, tot, red);
-  if (threadIdx.x == 0) {
-    if (det) {
-      double* o = det + ((size_t)f * nkb + kb) * 2;
-      o[0] = tot[0];
-      o[1] = tot[1];
-    } else {
-      atomicAdd(&facc[f * FA_COUNT + FA_E_QMMM_LR], tot[0]);
-      atomicAdd(&facc[f * FA_COUNT + FA_E_QQ_LR], tot[1]);
-    }
-  }
-}
-
 __global__ __launch_bounds__(256) void k_reduce_smm(Grid g, FrameArg fa, int a_chunk, int plain, int kmajor,
-                                                    const double2* __restrict__ spart,
-                                                    const double2* __restrict__ sabc,
-                                                    const double* __restrict__ kw, double2* __restrict__ smm,
-                                                    size_t smm_stride, double* __restrict__ facc,
-                                                    double* __restrict__ det) {
-  __shared__ double red[8];
+                                                    const double2* __restrict__ spart, double2* __restrict__ smm,
+                                                    size_t smm_stride) {
   const int f = blockIdx.y;
   const FrameDev fr = get_frame(fa, f);
-  reduce_smm_item(g, fr, f, blockIdx.x, gridDim.x, a_chunk, plain, kmajor, spart, sabc, kw, smm, smm_stride, facc,
-                  det, red);
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= g.KF) return;
+  const int col = k / g.NZ, iz = k - col * g.NZ;
+  const int nslots = plain ? 1 : (fr.nm + a_chunk - 1) / a_chunk;
+  const size_t idx = kmajor ? (size_t)k : (size_t)iz * g.NCOL + col;
+  // eight partials in flight per round trip (a load-add chain per slot left
+  // the kernel latency bound); the slots are still summed in order
+  const size_t sstride = (size_t)g.NZP * g.NCOL;
+  const double2* __restrict__ pp = spart + (size_t)fr.slot_base * sstride + idx;
+  double sr = 0.0, si = 0.0;
+  int sl = 0;
+  for (; sl + 8 <= nslots; sl += 8) {
+    double2 p[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) p[u] = pp[(size_t)(sl + u) * sstride];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      sr += p[u].x;
+      si += p[u].y;
+    }
+  }
+  for (; sl < nslots; sl++) {
+    const double2 p = pp[(size_t)sl * sstride];
+    sr += p.x;
+    si += p.y;
+  }
+  if (plain && fr.nm == 0) sr = si = 0.0;
+  smm[(size_t)f * smm_stride + k] = make_double2(sr, si);
 }
 
 hipError_t launch_reduce_smm(const Grid& g, const Tuning& t, const FrameArg& fa, int plain, double2* smm_out,
                              size_t smm_frame_stride, Work& w, hipStream_t s) {
   dim3 grid((g.KF + 255) / 256, fa.n_frames);
   const int kmajor = !plain && t.fwd_mode == 1;
-  hipLaunchKernelGGL(k_reduce_smm, grid, dim3(256), 0, s, g, fa, t.a_chunk, plain, kmajor, w.spart, w.sabc, w.kw,
-                     smm_out, smm_frame_stride, w.facc, w.det_smm);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !w.det_smm) return e;
-  return launch_det_reduce(fa, 0, 1, w.det_smm, (int)grid.x, 2, det_map({FA_E_QMMM_LR, FA_E_QQ_LR}), w.facc,
-                           FA_COUNT, s);
+  hipLaunchKernelGGL(k_reduce_smm, grid, dim3(256), 0, s, g, fa, t.a_chunk, plain, kmajor, w.spart, smm_out,
+                     smm_frame_stride);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ QM-site projection

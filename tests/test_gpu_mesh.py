@@ -1,0 +1,119 @@
+"""Gridded reciprocal sums against the CPU oracle where the mesh kernels can go
+wrong: few and odd atom counts, atoms on cell, tile and box faces, many atoms in
+one cell (more than one staging round and more than one position block), meshes
+of unequal and of the smallest size, frames without atoms, boxes whose Ewald
+weights fall off too little for the plan's mesh (dense sums then), and fixed
+order in deterministic plans.
+
+Tolerance: the aliasing stays below 1e-16 of the sum; FP64 rounding over up to
+1e5 terms as a random walk gives 3e2 x 1.1e-16 = 4e-14, and the gradients cancel
+about one digit: 1e-12 of each output's largest element."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2408_03273_amd import workloads as wl
+from paper_2408_03273_amd.ewald import EwaldConfig, Plan
+from tests import _harness as H
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-12
+
+
+def _system(seed, nq, nm, box, alpha, kmax, place=None):
+    s = wl.random_system(seed, nq, nm, box=box, alpha=alpha, rcut=0.45 * min(box), kmax=kmax, neutral=False)
+    if place is not None:
+        place(s, np.random.default_rng(seed + 1))
+    return s
+
+
+def _faces(s, rng):
+    """Atoms exactly on box faces, cell and tile boundaries and one ulp off them."""
+    N = 48
+    c = s.box / N * rng.choice([0, 4, 8, 16, 24, 40, 47], size=(s.nm, 3))
+    s.mm_pos[:] = c
+    s.mm_pos[::3] = np.nextafter(s.mm_pos[::3], np.inf)
+    s.mm_pos[1::3] = np.nextafter(s.mm_pos[1::3], -np.inf)
+    d = s.mm_pos - s.qm_pos.mean(0)
+    s.mm_pos[np.sqrt((d * d).sum(1)) < 5.0] = 0.0
+
+
+def _clump(s, rng):
+    """All atoms in two corners of the box: one mesh cell and the cell across the faces."""
+    s.mm_pos[:] = rng.uniform(-0.15, 0.15, (s.nm, 3))
+    s.mm_pos[::2] += s.box * 0.98
+
+
+CASES = [
+    # seed, nq, nm, box, alpha, kmax, placement (damping (pi m / (alpha L))^2 above each mesh's need)
+    (1, 2, 1, (20.0, 20.0, 20.0), 0.3, (8, 8, 8), None),
+    (2, 3, 65, (20.0, 21.0, 22.0), 0.3, (9, 10, 11), None),
+    (3, 5, 700, (16.0, 22.0, 30.0), 0.3, (8, 13, 17), None),
+    (4, 4, 400, (24.0, 24.0, 24.0), 0.3, (11, 11, 11), _faces),
+    (5, 4, 1111, (24.0, 24.0, 24.0), 0.3, (12, 12, 12), _clump),
+    (6, 6, 3001, (40.0, 30.0, 24.0), 0.25, (16, 12, 9), None),
+    (7, 1, 2500, (26.0, 27.0, 28.0), 0.45, (24, 20, 22), None),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"seed{c[0]}")
+def test_mesh_against_oracle(case, monkeypatch):
+    monkeypatch.setenv("MPEWALD_MESH", "1")
+    s = _system(*case)
+    plan = H.make_plan(s)
+    assert "mesh=" in plan.describe()
+    errs = H.compare(H.gpu_outputs(s, plan=plan), H.oracle_outputs(s), H.FWD_KEYS + H.BWD_KEYS)
+    print(f"[mesh] seed {case[0]} {plan.describe().split()[-1]}:", {k: f"{v:.1e}" for k, v in errs.items()}, flush=True)
+    assert max(errs.values()) <= TOL, errs
+
+
+def test_mesh_batch_with_an_empty_frame(monkeypatch):
+    monkeypatch.setenv("MPEWALD_MESH", "1")
+    fr = [_system(11, 3, 900, (22.0, 22.0, 22.0), 0.3, (10, 10, 10)),
+          _system(12, 2, 0, (20.0, 21.0, 20.0), 0.3, (10, 10, 10)),
+          _system(13, 4, 333, (18.0, 24.0, 21.0), 0.3, (10, 10, 10))]
+    cat = lambda k: torch.tensor(np.concatenate([getattr(f, k) for f in fr]), dtype=torch.float64,  # noqa: E731
+                                 device="cuda")
+    qo, mo = np.cumsum([0] + [f.nq for f in fr]), np.cumsum([0] + [f.nm for f in fr])
+    desc = [dict(box=f.box, n_qm=f.nq, n_mm=f.nm, qm_offset=int(qo[i]), mm_offset=int(mo[i]))
+            for i, f in enumerate(fr)]
+    plan = Plan(EwaldConfig(box=tuple(fr[0].box), alpha=0.3, rcut=fr[1].rcut, kmax=(10, 10, 10), max_qm=int(qo[-1]),
+                            max_mm=int(mo[-1]), max_frames=3))
+    args = (desc, cat("qm_pos"), cat("Q"), cat("mu"), cat("theta"), cat("mm_pos"), cat("q"))
+    out = plan.batch(*args)
+    for _ in range(2):  # replays
+        out = plan.batch(*args, out=out)
+    torch.cuda.synchronize()
+    for i, f in enumerate(fr):
+        f.rcut = fr[1].rcut
+        ref = H.oracle_outputs(f)
+        got = {k: out[k].cpu().numpy() for k in out}
+        q, m = slice(qo[i], qo[i + 1]), slice(mo[i], mo[i + 1])
+        got = dict(energy=got["energy"][i], phi=got["phi"][q], efield=got["efield"][q], efgrad=got["efgrad"][q],
+                   g_qm_pos=got["g_qm_pos"][q], g_Q=got["g_Q"][q], g_mu=got["g_mu"][q], g_theta=got["g_theta"][q],
+                   g_mm_pos=got["g_mm_pos"][m], g_mm_q=got["g_mm_q"][m])
+        errs = H.compare(got, ref, H.FWD_KEYS + H.BWD_KEYS)
+        assert max(errs.values()) <= TOL, (i, errs)
+
+
+def test_dense_sums_where_the_weights_fall_off_too_little(monkeypatch):
+    """set_box to a box of 2.2 times the edges leaves the band edge too strong
+    for the plan's mesh: the call takes the dense sums and stays exact."""
+    monkeypatch.setenv("MPEWALD_MESH", "1")
+    s = _system(21, 3, 500, (44.0, 44.0, 44.0), 0.3, (14, 14, 14))
+    s.rcut = 9.0
+    plan = Plan(EwaldConfig(box=(20.0, 20.0, 20.0), alpha=0.3, rcut=s.rcut, kmax=(14, 14, 14), max_qm=3, max_mm=500))
+    plan.set_box(s.box)
+    errs = H.compare(H.gpu_outputs(s, plan=plan), H.oracle_outputs(s), H.FWD_KEYS + H.BWD_KEYS)
+    assert max(errs.values()) <= TOL, errs
+
+
+def test_mesh_deterministic(monkeypatch):
+    monkeypatch.setenv("MPEWALD_MESH", "1")
+    s = _system(31, 4, 5000, (24.0, 25.0, 26.0), 0.3, (11, 11, 12))
+    plan = Plan(EwaldConfig(box=tuple(s.box), alpha=s.alpha, rcut=s.rcut, kmax=s.kmax, max_qm=s.nq, max_mm=s.nm,
+                            deterministic=True))
+    a = H.gpu_outputs(s, plan=plan)
+    for _ in range(3):
+        b = H.gpu_outputs(s, plan=plan)
+        assert all(np.array_equal(a[k], b[k]) for k in a)
