@@ -254,8 +254,11 @@ __global__ __launch_bounds__(256) void k_mesh_sort(Mesh m, FrameArg fa, const do
 // around the tile are staged in LDS 64 at a time with zeros on both sides of
 // their taps, so that a point off the support reads a zero without a test
 // (the next 64 are on their way from memory meanwhile); each wave lists the
-// atoms whose 16^3 points meet its part, with the three LDS addresses of its
-// first point.  Operand reads from LDS and the matrix cores bound it about
+// atoms whose 16^3 points meet its part, with the three LDS byte addresses of
+// its first point.  The products phi_y phi_z of a step are formed before it, so
+// that its four matrix instructions follow each other (16 frames of 100 000
+// charges on a 112^3 mesh: 1.78 ms with the products between them, 1.67 ms so;
+// the matrix cores alone 0.59 ms).  Operand reads from LDS and the matrix cores bound it about
 // equally: a 4 x 4 part has less work outside the support (31 19 19 / 16^3 =
 // 2.7 times the useful multiply-adds, 3.3 here) but twice the x reads.
 // A staged atom: [15 zeros | x taps | 15 zeros | y taps | 7 zeros | z taps], each
@@ -321,8 +324,8 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
   const int total = row_off[kSpreadRows];
   const int oy = 4 * (wave & 1), oz = 8 * (wave >> 1);
   const int li = lane & 15, lk = lane >> 4;
-  // this lane's point relative to the wave's first one, in doubles
-  const int xq = li, yq = li >> 2, zq = li & 3;
+  // this lane's point relative to the wave's first one, in bytes
+  const int xq = 8 * li, yq = 8 * (li >> 2), zq = 8 * (li & 3);
   v4d acc[2][2];
 #pragma unroll
   for (int u = 0; u < 2; u++) acc[u][0] = acc[u][1] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -400,39 +403,49 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
         const int rx = (e & 255) - 16, ry = ((e >> 8) & 255) - 16 - oy, rz = ((e >> 16) & 255) - 16 - oz;
         hit = rx <= 15 && ry >= -15 && ry <= 3 && rz >= -15 && rz <= 7;
         // tap j of an axis sits at its first tap + j; the part's first point reads tap -r
-        const int b = lane * kSpreadAtom;
-        ad = make_int4(b + kSpreadX - rx, b + kSpreadY - ry, b + kSpreadZ - rz, 0);
+        const int b = 8 * lane * kSpreadAtom;
+        ad = make_int4(b + 8 * (kSpreadX - rx), b + 8 * (kSpreadY - ry), b + 8 * (kSpreadZ - rz), 0);
       }
       const unsigned long long mask = __ballot(hit);
       const int cnt = (int)__popcll(mask);
       int4* lw = list[wave];
       if (hit) lw[__popcll(mask & ((1ull << lane) - 1ull))] = ad;
       // padding to whole steps and for the reads ahead: the zeros at the end
-      if (lane < 24) lw[cnt + lane] = make_int4(64 * kSpreadAtom, 64 * kSpreadAtom, 64 * kSpreadAtom, 0);
+      if (lane < 24) lw[cnt + lane] = make_int4(512 * kSpreadAtom, 512 * kSpreadAtom, 512 * kSpreadAtom, 0);
       lds_wave_sync();
-      // two groups of four atoms per step; the operands of the next step and
-      // the addresses of the one after are read while this step is contracted
+      // two groups of four atoms per step: the operands of the next step are read and
+      // the list entries of the one after while this step is contracted
+      const char* __restrict__ tb = (const char*)tp;
+      auto at = [&](int byte, int u) { return ((const double*)(tb + byte))[u]; };
       int4 e0 = lw[lk], e1 = lw[4 + lk];
-      double o0[4] = {tp[e0.x + xq], tp[e0.y + yq], tp[e0.z + zq], tp[e0.z + zq + 4]};
-      double o1[4] = {tp[e1.x + xq], tp[e1.y + yq], tp[e1.z + zq], tp[e1.z + zq + 4]};
+      double x0 = at(e0.x + xq, 0), x1 = at(e1.x + xq, 0);
+      double p[4];
+      {
+        const double y0 = at(e0.y + yq, 0), y1 = at(e1.y + yq, 0);
+        p[0] = y0 * at(e0.z + zq, 0);
+        p[1] = y0 * at(e0.z + zq, 4);
+        p[2] = y1 * at(e1.z + zq, 0);
+        p[3] = y1 * at(e1.z + zq, 4);
+      }
       e0 = lw[8 + lk];
       e1 = lw[12 + lk];
       for (int s = 0; s < cnt; s += 8) {
-        const double n0[4] = {tp[e0.x + xq], tp[e0.y + yq], tp[e0.z + zq], tp[e0.z + zq + 4]};
-        const double n1[4] = {tp[e1.x + xq], tp[e1.y + yq], tp[e1.z + zq], tp[e1.z + zq + 4]};
+        const double n0[4] = {at(e0.x + xq, 0), at(e0.y + yq, 0), at(e0.z + zq, 0), at(e0.z + zq, 4)};
+        const double n1[4] = {at(e1.x + xq, 0), at(e1.y + yq, 0), at(e1.z + zq, 0), at(e1.z + zq, 4)};
         e0 = lw[s + 16 + lk];
         e1 = lw[s + 20 + lk];
         __builtin_amdgcn_sched_barrier(0);
-        acc[0][0] = mfma(o0[0], o0[1] * o0[2], acc[0][0]);
-        acc[0][1] = mfma(o0[0], o0[1] * o0[3], acc[0][1]);
-        acc[1][0] = mfma(o1[0], o1[1] * o1[2], acc[1][0]);
-        acc[1][1] = mfma(o1[0], o1[1] * o1[3], acc[1][1]);
+        acc[0][0] = mfma(x0, p[0], acc[0][0]);
+        acc[0][1] = mfma(x0, p[1], acc[0][1]);
+        acc[1][0] = mfma(x1, p[2], acc[1][0]);
+        acc[1][1] = mfma(x1, p[3], acc[1][1]);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-          o0[u] = n0[u];
-          o1[u] = n1[u];
-        }
+        x0 = n0[0];
+        x1 = n1[0];
+        p[0] = n0[1] * n0[2];
+        p[1] = n0[1] * n0[3];
+        p[2] = n1[1] * n1[2];
+        p[3] = n1[1] * n1[3];
       }
     }
     __syncthreads();  // the staged atoms are replaced
@@ -646,7 +659,7 @@ __global__ __launch_bounds__(256) void k_mesh_wk(Mesh m, int KF, const double2* 
 }
 
 // ------------------------------------------------------------------ reading the mesh at the charges
-// Persistent blocks of 8 waves (one per CU) take tiles of 8 x 8 x 16 mesh
+// Persistent blocks of 12 waves (one per CU) take tiles of 8 x 8 x 16 mesh
 // cells in turn.  A tile's atoms read 23 x 23 x 32 mesh points, which are
 // staged in LDS (135 KB; tiles start at cells 16 k + 8 in z, so that a row of 32
 // points is two cache lines); the next tile's points are loaded into registers
@@ -657,11 +670,15 @@ __global__ __launch_bounds__(256) void k_mesh_wk(Mesh m, int KF, const double2* 
 // into scalar registers.  Each lane sums its column over x with both (128
 // multiply-adds for the atom's 4096 points), then the y and z factors give
 // potential and gradient, reduced over the wave.  The 4096 reads per atom
-// bound it: 32 KB per atom from LDS at 128 bytes per cycle and CU.
+// bound it: 32 KB per atom from LDS at 128 bytes per cycle and CU.  Three waves
+// per SIMD with the reads of one x point ahead cover each other's start and end
+// of an atom better than two with the reads of two points ahead (112^3 mesh,
+// 16 frames of 100 000 charges: 1.60 ms with 8 waves, 1.45 ms with 12; the LDS
+// reads alone 0.85 ms); a fourth wave does not fit the registers.
 static constexpr int kGatherX = 8, kGatherY = 8, kGatherZ = 16;                             // cells of a tile
 static constexpr int kGatherWX = kGatherX + 15, kGatherWY = kGatherY + 15, kGatherWZ = 32;  // staged points
 static constexpr int kGatherBlocks = 256;                                                   // one per CU
-static constexpr int kGatherWaves = 8;
+static constexpr int kGatherWaves = 12;
 static constexpr int kGatherRows = kGatherWX * kGatherWY;
 static constexpr int kGatherRounds = (kGatherRows + 4 * kGatherWaves - 1) / (4 * kGatherWaves);  // 16 lanes per row
 
@@ -825,26 +842,22 @@ __global__ __launch_bounds__(64 * kGatherWaves) void k_mesh_gather(Mesh m, Frame
     dz -= dz >= m.N[2] ? m.N[2] : 0;
     const double* w0 = (const double*)win +
                        (((cx & 1023) - g.X0) * kGatherWY + (cx >> 10 & 1023) - g.Y0 + ly) * kGatherWZ + dz + 1 + lz;
-    // the reads of two x points are issued ahead of the multiply-adds of the previous two
-    double A[4] = {0.0, 0.0, 0.0, 0.0}, D[4] = {0.0, 0.0, 0.0, 0.0}, w[2][8];
+    // the reads of the next x point are issued ahead of the multiply-adds of this one
+    double A[4] = {0.0, 0.0, 0.0, 0.0}, D[4] = {0.0, 0.0, 0.0, 0.0}, w[2][4];
 #pragma unroll
-    for (int e = 0; e < 8; e++) w[0][e] = w0[((e >> 2) * kGatherWY + 4 * (e & 3)) * kGatherWZ];
+    for (int q = 0; q < 4; q++) w[0][q] = w0[4 * q * kGatherWZ];
 #pragma unroll
-    for (int h = 0; h < 8; h++) {
-      if (h < 7) {
+    for (int x = 0; x < 16; x++) {
+      if (x < 15) {
 #pragma unroll
-        for (int e = 0; e < 8; e++)
-          w[(h + 1) & 1][e] = w0[((2 * h + 2 + (e >> 2)) * kGatherWY + 4 * (e & 3)) * kGatherWZ];
+        for (int q = 0; q < 4; q++) w[(x + 1) & 1][q] = w0[((x + 1) * kGatherWY + 4 * q) * kGatherWZ];
       }
       __builtin_amdgcn_sched_barrier(0);
+      const double xv = lane_value(pv, x), xd = lane_value(pd, x);
 #pragma unroll
-      for (int x = 0; x < 2; x++) {
-        const double xv = lane_value(pv, 2 * h + x), xd = lane_value(pd, 2 * h + x);
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          A[q] = fma(xv, w[h & 1][4 * x + q], A[q]);
-          D[q] = fma(xd, w[h & 1][4 * x + q], D[q]);
-        }
+      for (int q = 0; q < 4; q++) {
+        A[q] = fma(xv, w[x & 1][q], A[q]);
+        D[q] = fma(xd, w[x & 1][q], D[q]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
