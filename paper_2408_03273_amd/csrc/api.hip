@@ -579,7 +579,7 @@ ewald_status_t seq_forward_tail(const Seq& q, const double* Q, const double* mu,
     LCHK(launch_mesh_smm(pl->mesh, pl->g, q.fa, smm, smm_stride, pl->w, q.s));
   else
     LCHK(launch_reduce_smm(pl->g, pl->t, q.fa, q.plain, smm, smm_stride, pl->w, q.s));
-  LCHK(launch_project_qm(pl->g, q.fa, q.max_nq, q.total_nq, smm, smm_stride, Q, mu, theta, mode, q.qmqm, pl->w, q.s));
+  LCHK(launch_project_qm(pl->g, q.fa, q.max_nq, smm, smm_stride, Q, mu, theta, mode, q.qmqm, pl->w, q.s));
   if (!early) {  // early: real space and QM-QM were launched before the reciprocal work
     if (q.cells)
       LCHK(launch_real_cells(pl->g, q.fa, q.max_nq, pl->cap_qm, pl->cap_mm, 0, q.fp32, pl->w, q.s));
@@ -1121,7 +1121,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
     STEP(launch_real_mm(g, q.fa, n_qm, n_mm, plan->cap_qm, plan->cap_mm, q.fp32, w, s, q.mm_groups));
   }
   STEP(launch_reduce_mm(g, plan->t, q.fa, n_mm, plan->cap_mm, g_mm_xyz, g_mm_q, w, s));
-  STEP(launch_project_qm(g, q.fa, n_qm, n_qm, cv.smm, g.KF, Q, mu, theta, 1, q.qmqm, w, s));
+  STEP(launch_project_qm(g, q.fa, n_qm, cv.smm, g.KF, Q, mu, theta, 1, q.qmqm, w, s));
   if (!q.cells) STEP(launch_real_qm(g, q.fa, n_qm, n_mm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s));
   if (q.qmqm && n_qm > 0) STEP(launch_qmqm(g, q.fa, n_qm, plan->cap_qm, Q, mu, theta, w, s));
   STEP(launch_finalize_bwd(q.fa, n_qm, cv.site, gE, q.qmqm, g_qm_xyz, g_Q, g_mu, g_theta, w, s));
@@ -1404,8 +1404,7 @@ extern "C" ewald_status_t ewald_moments_update(ewald_plan* plan, const void* ctx
   if (st != EWALD_OK) return st;
   LCHK(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, 0, w, s));
   if (q.qmqm && n_qm > 0) {
-    // (the projection's QM-MM sums, taken from whatever S_MM is there, are not used)
-    LCHK(launch_project_qm(g, q.fa, n_qm, n_qm, w.smm, g.KF, Q, mu, theta, 1, 1, w, s));
+    LCHK(launch_project_qm(g, q.fa, n_qm, nullptr, 0, Q, mu, theta, 1, 1, w, s));
     LCHK(launch_qmqm(g, q.fa, n_qm, plan->cap_qm, Q, mu, theta, w, s));
   }
   LCHK(launch_finalize_moments(q.fa, Q, mu, theta, q.qmqm, cv.site, energy, g_Q, g_mu, g_theta, w, s));

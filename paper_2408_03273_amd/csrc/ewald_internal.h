@@ -277,8 +277,8 @@ hipError_t launch_mesh_force(const Mesh& m, const Grid& g, const FrameArg& fa, i
 hipError_t launch_sfac_mm_plain(const Grid& g, const FrameArg& fa, int cap_mm, Work& w, hipStream_t s);
 hipError_t launch_reduce_smm(const Grid& g, const Tuning& t, const FrameArg& fa, int plain, double2* smm_out,
                              size_t smm_frame_stride, Work& w, hipStream_t s);
-// backward: 0 forward sums, 1 adjoint sums, 2 both
-hipError_t launch_project_qm(const Grid& g, const FrameArg& fa, int max_nq, int total_nq, const double2* smm,
+// backward: 0 forward sums, 1 adjoint sums, 2 both; smm null: the QM-QM sums only
+hipError_t launch_project_qm(const Grid& g, const FrameArg& fa, int max_nq, const double2* smm,
                              size_t smm_frame_stride, const double* Q, const double* mu, const double* theta,
                              int backward, int qmqm, Work& w, hipStream_t s);
 hipError_t launch_force_mm(const Grid& g, const Tuning& t, const FrameArg& fa, int max_nm, int cap_mm, Work& w,

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "ewald_internal.h"
+#include "lanes.h"
 
 namespace mpe {
 
@@ -1114,223 +1115,324 @@ hipError_t launch_reduce_smm(const Grid& g, const Tuning& t, const FrameArg& fa,
 // site from S_MM.  Backward: the QM-MM long-range gradient with the
 // effective moments, and the QM-QM long-range gradient and moment
 // derivatives of the order-2 truncated image energy.
-// LDS doubles of the projection's block sums
-template <int BWD>
-constexpr int project_lds_doubles() {
-  return 4 * (BWD == 0 ? 10 : BWD == 1 ? 16 : 26);
+//
+// All of them are sums over k of w(k) kx^a ky^b kz^c e_j(k) conj(Z(k)) with
+// Z = S_MM, T1 = A + B + C, T2 = A + B or A.  With e_j = e_xy(column) e_z(nz)
+// only the nz sums of a column depend on both the site and every k:
+//   Z_c(j, column) = sum_nz w nz^c conj(Z) e^{i kz0 nz z_j}
+//     = sum_p p^c { (U+ +- U-) cos(p kz0 z_j) + i (U+ -+ U-) sin(p kz0 z_j) },
+// U+- = w conj(Z) at nz = +-p, upper signs for even c.  These are products of
+// a (column x p) and a (p x site) matrix and run on the matrix cores, 13
+// complex sums (S_MM c = 0..3, T1 0..1, T2 0..2, A 0..3) as 26 real
+// accumulators of 16 columns x 16 sites; then 16 (site, column) pairs per lane row
+// take the column's phase and powers of kx, ky.  A lane's four accumulator
+// elements belong to one site, so the column sums stay in its registers until
+// the wave ends.
+//
+// A wave takes 16 sites, a range of column groups and one of two
+// kinds of sums (0: S_MM and T1, 1: T2 and A; 24 and 28 matrix instructions per
+// four p), which keeps a wave at 256 registers, two waves per SIMD.  Bound by
+// the matrix cores; blocks that read the same columns run on the same XCD.
+// Measured against one thread per (k, two sites) with all sums per k on the vector
+// units: 16 frames of 80 sites at kmax 32 1.00 -> 0.29 ms (0.13 ms of matrix
+// instructions), one of 40 sites at kmax 24 50 -> 12.5 us, its QM-QM sums alone
+// 35 -> 10 us.  (One wave per block left those at 25 us, with four times the atomics.)
+DEV double2 cplus(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+
+template <int NZS>
+struct ZSums {
+  v4d re[NZS], im[NZS];
+};
+
+// one four-p step of the z sums of Z: c = 0 .. NC - 1
+template <int NC>
+DEV void z_step(ZSums<NC>& z, double2 Zp, double2 Zm, double wp, double wm, double p, double p2, double cs, double sn) {
+  const double upr = wp * Zp.x, upi = -wp * Zp.y, umr = wm * Zm.x, umi = -wm * Zm.y;
+  const double er = upr + umr, ei = upi + umi, dr = upr - umr, di = upi - umi;
+  const double ndi = umi - upi, nei = -ei;
+  z.re[0] = mfma4(er, cs, z.re[0]);
+  z.im[0] = mfma4(ei, cs, z.im[0]);
+  if (NC > 1) {
+    z.re[1] = mfma4(p * dr, cs, z.re[1]);
+    z.im[1] = mfma4(p * di, cs, z.im[1]);
+  }
+  if (NC > 2) {
+    z.re[2] = mfma4(p2 * er, cs, z.re[2]);
+    z.im[2] = mfma4(p2 * ei, cs, z.im[2]);
+  }
+  if (NC > 3) {
+    z.re[3] = mfma4(p2 * (p * dr), cs, z.re[3]);
+    z.im[3] = mfma4(p2 * (p * di), cs, z.im[3]);
+  }
+  z.re[0] = mfma4(ndi, sn, z.re[0]);
+  z.im[0] = mfma4(dr, sn, z.im[0]);
+  if (NC > 1) {
+    z.re[1] = mfma4(p * nei, sn, z.re[1]);
+    z.im[1] = mfma4(p * er, sn, z.im[1]);
+  }
+  if (NC > 2) {
+    z.re[2] = mfma4(p2 * ndi, sn, z.re[2]);
+    z.im[2] = mfma4(p2 * dr, sn, z.im[2]);
+  }
+  if (NC > 3) {
+    z.re[3] = mfma4(p2 * (p * nei), sn, z.re[3]);
+    z.im[3] = mfma4(p2 * (p * er), sn, z.im[3]);
+  }
 }
 
-// One item: sites sb S .. sb S + S - 1 of frame f, the k items of block pc of
-// n_pc; red holds project_lds_doubles<BWD>().
-template <int BWD, int S>
-DEV void project_qm_item(const Grid& g, const FrameDev& fr, int f, int sb, int pc, int n_pc,
-                         const double2* __restrict__ smm, size_t smm_stride, const double* __restrict__ Q,
-                         const double* __restrict__ mu, const double* __restrict__ theta,
-                         const double* __restrict__ qeff, const double2* __restrict__ qtab,
-                         const double2* __restrict__ sabc, const double* __restrict__ kw, int qmqm,
-                         double* __restrict__ qacc, double* __restrict__ det, double* red) {
-  // S sites per block: the per-k data (weight, S_MM, A/B/C) is loaded once per
-  // k and applied to each site; the sites' moments are block-uniform
-  const int j0 = sb * S;
-  if (j0 >= fr.nq) return;
-  const int ns = min(S, fr.nq - j0);  // uniform
-  // BWD: 0 forward (10 sums), 1 adjoint (16), 2 both (26, adjoint after the forward ones)
-  constexpr int NV = BWD == 0 ? 10 : BWD == 1 ? 16 : 26;
-  constexpr int OB = BWD == 2 ? 10 : 0;
-  double acc[S][NV];
+template <int NC>
+DEV void z_clear(ZSums<NC>& z) {
 #pragma unroll
-  for (int u = 0; u < S; u++)
-#pragma unroll
-    for (int t = 0; t < NV; t++) acc[u][t] = 0.0;
-  struct Mom {
-    double Qe, m0, m1, m2, t0, t1, t2, t3, t4, t5, Qo, o0, o1, o2, u0, u1, u2, u3, u4, u5;
+  for (int c = 0; c < NC; c++) z.re[c] = z.im[c] = v4d{0.0, 0.0, 0.0, 0.0};
+}
+
+// The sums' slots: 0 phi, 1-3 dphi, 4-9 H; 10-12 QM-MM gradient, 13-15 QM-QM
+// gradient, 16 dQ, 17-19 dmu, 20-25 dtheta.
+// BWD: 0 forward slots, 1 adjoint slots, 2 both; HS: with S_MM; QQ: with the QM-QM sums
+template <int BWD, bool HS, bool QQ, int KIND>
+DEV void project_wave(const Grid& g, const FrameDev& fr, int f, int lane, int tile, int g0, int g1, int s0, int s1,
+                      const double2* __restrict__ smm, size_t smm_stride, const double* __restrict__ Q,
+                      const double* __restrict__ mu, const double* __restrict__ theta,
+                      const double* __restrict__ qeff, const double2* __restrict__ qtab,
+                      const double2* __restrict__ sabc, const double* __restrict__ kw, double (&o)[28]) {
+  constexpr bool WS = KIND == 0 && HS, W1 = KIND == 0 && QQ, W2 = KIND == 1;
+  constexpr bool ABC = W1 || W2;
+  const int li = lane & 15, lk = lane >> 4;
+  const int row = fr.qoff + min(16 * tile + li, fr.nq - 1);
+  const double2* __restrict__ qrow = qtab + (size_t)row * g.R;
+  const double2* __restrict__ zrow = qrow + g.NX + g.NY + g.mz;
+  const double* __restrict__ kwf = kw + (size_t)f * g.KF;
+  const double2* __restrict__ sf = smm + (size_t)f * smm_stride;
+  const double2* __restrict__ abcf = sabc + (size_t)f * g.KF * 3;
+  struct In {
+    double wp, wm;
+    double2 Sp, Sm, Ap, Am, Bp, Bm, Cp, Cm, ez;
   };
-  Mom mo[S];
-  const double2* row[S];
-#pragma unroll
-  for (int u = 0; u < S; u++) {
-    const int r = fr.qoff + min(j0 + u, fr.nq - 1);
-    row[u] = qtab + (size_t)r * g.R;
-    Mom& m = mo[u];
-    m = Mom{};
-    if (BWD) {
-      const double* qe = qeff + 10 * (size_t)r;
-      m.Qe = qe[0]; m.m0 = qe[1]; m.m1 = qe[2]; m.m2 = qe[3];
-      m.t0 = qe[4]; m.t1 = qe[5]; m.t2 = qe[6]; m.t3 = qe[7]; m.t4 = qe[8]; m.t5 = qe[9];
-      m.Qo = Q[r]; m.o0 = mu[3 * (size_t)r]; m.o1 = mu[3 * (size_t)r + 1]; m.o2 = mu[3 * (size_t)r + 2];
-      const double* th = theta + 6 * (size_t)r;
-      m.u0 = th[0]; m.u1 = th[1]; m.u2 = th[2]; m.u3 = th[3]; m.u4 = th[4]; m.u5 = th[5];
+  // the step's data of column li of the group and p = 4 s + lk; p > mz, the
+  // second sign of p = 0 and columns past the last carry zero weight
+  auto load = [&](int grp, int s) {
+    In v;
+    const int p = 4 * s + lk, pc = min(p, g.mz), col = 16 * grp + li, cc = min(col, g.NCOL - 1);
+    const int kp = cc * g.NZ + g.mz + pc, km = kp - 2 * pc;
+    const bool live = p <= g.mz && col < g.NCOL;
+    v.wp = kwf[kp];
+    v.wm = kwf[km];
+    if (WS) {
+      v.Sp = sf[kp];
+      v.Sm = sf[km];
     }
-  }
-  // thread item = (column, p = |nz|): k = (nx, ny, +p) and (nx, ny, -p) share e^{i(kx x + ky y)}
-  const int NP = g.mz + 1;
-  const int n_items = g.NCOL * NP;
-  for (int t = pc * 256 + threadIdx.x; t < n_items; t += n_pc * 256) {
-    const int col = t / NP, p = t - col * NP;
-    const int nx = col / g.NY, iy = col - nx * g.NY;
-    const int ny = iy - g.my;
-    double2 exy[S], ez[S];
-#pragma unroll
-    for (int u = 0; u < S; u++) {
-      exy[u] = cmul(row[u][nx], row[u][g.NX + iy]);
-      ez[u] = row[u][g.NX + g.NY + g.mz + p];
-    }
-    // both signs of nz at once, without data-dependent branches, so that all
-    // the item's loads are issued together (one round trip per item); the
-    // second sign of p = 0 and k outside the half space carry zero weight
-    const int k0 = col * g.NZ + g.mz;
-    double wv[2];
-    double2 Sv[2], Av[2], Bv[2], Cv[2];
-#pragma unroll
-    for (int sg = 0; sg < 2; sg++) {
-      const int k = k0 + (sg ? -p : p);
-      wv[sg] = (sg && p == 0) ? 0.0 : kw[(size_t)f * g.KF + k];
-      Sv[sg] = smm[(size_t)f * smm_stride + k];
-      Av[sg] = Bv[sg] = Cv[sg] = make_double2(0.0, 0.0);
-      if (BWD != 0 && qmqm) {
-        const double2* abc = sabc + ((size_t)f * g.KF + k) * 3;
-        Av[sg] = abc[0];
-        Bv[sg] = abc[1];
-        Cv[sg] = abc[2];
+    if (ABC) {
+      const double2 *ap = abcf + 3 * (size_t)kp, *am = abcf + 3 * (size_t)km;
+      v.Ap = ap[0];
+      v.Bp = ap[1];
+      v.Am = am[0];
+      v.Bm = am[1];
+      if (W1) {
+        v.Cp = ap[2];
+        v.Cm = am[2];
       }
     }
+    v.ez = zrow[pc];
+    v.wp = live ? v.wp : 0.0;
+    v.wm = live && p > 0 ? v.wm : 0.0;
+    return v;
+  };
+  const double kz0 = 2.0 * kPi * fr.inv_box[2];
+  In nx_ = load(g0, s0);
+  for (int grp = g0; grp < g1; grp++) {
+    ZSums<BWD == 0 ? 3 : 4> zs;
+    ZSums<2> z1;
+    ZSums<3> z2;
+    ZSums<4> za;
+    if (WS) z_clear(zs);
+    if (W1) z_clear(z1);
+    if (W2) {
+      z_clear(z2);
+      z_clear(za);
+    }
+    for (int s = s0; s < s1; s++) {
+      const In v = nx_;
+      const bool last = s + 1 == s1;
+      if (!last || grp + 1 < g1) nx_ = load(last ? grp + 1 : grp, last ? s0 : s + 1);
+      const double p = (double)(4 * s + lk), p2 = p * p;
+      if (WS) z_step(zs, v.Sp, v.Sm, v.wp, v.wm, p, p2, v.ez.x, v.ez.y);
+      if (ABC) {
+        const double2 T2p = cplus(v.Ap, v.Bp), T2m = cplus(v.Am, v.Bm);
+        if (W1) z_step(z1, cplus(T2p, v.Cp), cplus(T2m, v.Cm), v.wp, v.wm, p, p2, v.ez.x, v.ez.y);
+        if (W2) {
+          z_step(z2, T2p, T2m, v.wp, v.wm, p, p2, v.ez.x, v.ez.y);
+          z_step(za, v.Ap, v.Am, v.wp, v.wm, p, p2, v.ez.x, v.ez.y);
+        }
+      }
+    }
+    // lane: site li, columns lk + 4 r
 #pragma unroll
-    for (int sg = 0; sg < 2; sg++) {
-      const int nz = sg ? -p : p;
-      const double w = wv[sg];
-      const double kx = 2.0 * kPi * nx * fr.inv_box[0], ky = 2.0 * kPi * ny * fr.inv_box[1],
-                   kz = 2.0 * kPi * nz * fr.inv_box[2];
-      const double2 Sk = Sv[sg], A = Av[sg], B = Bv[sg], C = Cv[sg];
-#pragma unroll
-      for (int u = 0; u < S; u++) {
-        if (u >= ns) break;  // uniform
-        const Mom& m = mo[u];
-        double* ac = acc[u];
-        const double2 e = cmul(exy[u], sg ? cconj(ez[u]) : ez[u]);
-        // Y = e conj(S)
-        const double yr = e.x * Sk.x + e.y * Sk.y, yi = e.y * Sk.x - e.x * Sk.y;
+    for (int r = 0; r < 4; r++) {
+      const int col = min(16 * grp + lk + 4 * r, g.NCOL - 1);  // (sums of columns past the last are zero)
+      const int nx = col / g.NY, iy = col - nx * g.NY;
+      const double2 e = cmul(qrow[nx], qrow[g.NX + iy]);
+      const double kx = 2.0 * kPi * nx * fr.inv_box[0], ky = 2.0 * kPi * (iy - g.my) * fr.inv_box[1];
+      // phase times the sums of kz^c
+      auto term = [&](const v4d& re, const v4d& im, double k) { return cmul(make_double2(k * e.x, k * e.y), make_double2(re[r], im[r])); };
+      if (WS) {
+        const double2 P0 = term(zs.re[0], zs.im[0], 1.0), P1 = term(zs.re[1], zs.im[1], kz0),
+                      P2 = term(zs.re[2], zs.im[2], kz0 * kz0);
         if (BWD != 1) {
-          ac[0] += w * yr;
-          ac[1] -= w * kx * yi;
-          ac[2] -= w * ky * yi;
-          ac[3] -= w * kz * yi;
-          const double h = -0.5 * w * yr;
-          ac[4] += h * kx * kx;
-          ac[5] += h * kx * ky;
-          ac[6] += h * kx * kz;
-          ac[7] += h * ky * ky;
-          ac[8] += h * ky * kz;
-          ac[9] += h * kz * kz;
+          o[0] += P0.x;
+          o[1] -= kx * P0.y;
+          o[2] -= ky * P0.y;
+          o[3] -= P1.y;
+          const double h = -0.5 * P0.x, h1 = -0.5 * P1.x;
+          o[4] += h * kx * kx;
+          o[5] += h * kx * ky;
+          o[6] += h1 * kx;
+          o[7] += h * ky * ky;
+          o[8] += h1 * ky;
+          o[9] -= 0.5 * P2.x;
         }
         if (BWD != 0) {
-          // QM-MM: d/dR of Re[(Q' + i k.mu' - 1/2 k.th'.k) Y] = k Re[i (..) Y]
-          const double kthk = kx * kx * m.t0 + ky * ky * m.t3 + kz * kz * m.t5 +
-                              2.0 * (kx * ky * m.t1 + kx * kz * m.t2 + ky * kz * m.t4);
-          const double wr = m.Qe - 0.5 * kthk, wi = kx * m.m0 + ky * m.m1 + kz * m.m2;
-          const double gr = -(wr * yi + wi * yr);
-          ac[OB + 0] += w * kx * gr;
-          ac[OB + 1] += w * ky * gr;
-          ac[OB + 2] += w * kz * gr;
-          if (qmqm) {
-            const double kmu = kx * m.o0 + ky * m.o1 + kz * m.o2;
-            const double kthko = kx * kx * m.u0 + ky * ky * m.u3 + kz * kz * m.u5 +
-                                 2.0 * (kx * ky * m.u1 + kx * kz * m.u2 + ky * kz * m.u4);
-            // a_j = Q e, b_j = i kmu e, c_j = -1/2 kthk e
-            const double ajr = m.Qo * e.x, aji = m.Qo * e.y;
-            const double bjr = -kmu * e.y, bji = kmu * e.x;
-            const double cjr = -0.5 * kthko * e.x, cji = -0.5 * kthko * e.y;
-            const double T1r = A.x + B.x + C.x, T1i = A.y + B.y + C.y;
-            const double T2r = A.x + B.x, T2i = A.y + B.y;
-            // Im[a_j conj(T1) + b_j conj(T2) + c_j conj(A)]
-            const double zi = (aji * T1r - ajr * T1i) + (bji * T2r - bjr * T2i) + (cji * A.x - cjr * A.y);
-            ac[OB + 3] -= w * kx * zi;
-            ac[OB + 4] -= w * ky * zi;
-            ac[OB + 5] -= w * kz * zi;
-            ac[OB + 6] += w * (e.x * T1r + e.y * T1i);
-            const double ime = e.y * T2r - e.x * T2i;
-            ac[OB + 7] -= w * kx * ime;
-            ac[OB + 8] -= w * ky * ime;
-            ac[OB + 9] -= w * kz * ime;
-            const double h = -0.5 * w * (e.x * A.x + e.y * A.y);
-            ac[OB + 10] += h * kx * kx;
-            ac[OB + 11] += h * kx * ky;
-            ac[OB + 12] += h * kx * kz;
-            ac[OB + 13] += h * ky * ky;
-            ac[OB + 14] += h * ky * kz;
-            ac[OB + 15] += h * kz * kz;
-          }
+          // d/dR of Re[(Q' + i k.mu' - 1/2 k.th'.k) Y] = k Re[i (..) Y], Y = e conj(S_MM)
+          const double2 P3 = term(zs.re[BWD == 0 ? 2 : 3], zs.im[BWD == 0 ? 2 : 3], kz0 * kz0 * kz0);
+          const double* __restrict__ qe = qeff + 10 * (size_t)row;
+          const double a0 = qe[0] - 0.5 * (kx * kx * qe[4] + ky * ky * qe[7]) - kx * ky * qe[5];
+          const double a1 = -(kx * qe[6] + ky * qe[8]), a2 = -0.5 * qe[9];
+          const double b0 = kx * qe[1] + ky * qe[2], b1 = qe[3];
+          const double gr = a0 * P0.y + a1 * P1.y + a2 * P2.y + b0 * P0.x + b1 * P1.x;
+          o[10] -= kx * gr;
+          o[11] -= ky * gr;
+          o[12] -= a0 * P1.y + a1 * P2.y + a2 * P3.y + b0 * P1.x + b1 * P2.x;
         }
       }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < S; u++) {
-    if (u >= ns) break;  // uniform
-    double tot[NV];
-    block_sum256_lds<NV>(acc[u], tot, red);
-    if (threadIdx.x == 0 && det) {
-      // partial sums of this block, summed over the blocks in order afterwards
-      double* o = det + ((size_t)(fr.qoff + j0 + u) * n_pc + pc) * 26;
-      for (int t = 0; t < NV; t++) o[t] = tot[t];
-    } else if (threadIdx.x == 0) {
-      double* qa = qacc + (size_t)(fr.qoff + j0 + u) * QA_STRIDE;
-      if (BWD != 1) {
-        atomicAdd(&qa[QA_PHI_LR], tot[0]);
-        for (int t = 0; t < 3; t++) atomicAdd(&qa[QA_DPHI_LR + t], tot[1 + t]);
-        for (int t = 0; t < 6; t++) atomicAdd(&qa[QA_H_LR + t], tot[4 + t]);
+      if (W1) {
+        // Im[a conj(T1)], a = Q e
+        const double2 R0 = term(z1.re[0], z1.im[0], 1.0), R1 = term(z1.re[1], z1.im[1], kz0);
+        const double q = Q[row];
+        o[13] -= kx * q * R0.y;
+        o[14] -= ky * q * R0.y;
+        o[15] -= q * R1.y;
+        o[16] += R0.x;
       }
-      if (BWD != 0) {
-        for (int t = 0; t < 3; t++) atomicAdd(&qa[QA_G_QMMM_LR + t], tot[OB + t]);
-        if (qmqm) {
-          for (int t = 0; t < 3; t++) atomicAdd(&qa[QA_G_QQ_LR + t], tot[OB + 3 + t]);
-          atomicAdd(&qa[QA_DQ_QQ_LR], tot[OB + 6]);
-          for (int t = 0; t < 3; t++) atomicAdd(&qa[QA_DMU_QQ_LR + t], tot[OB + 7 + t]);
-          for (int t = 0; t < 6; t++) atomicAdd(&qa[QA_DTH_QQ_LR + t], tot[OB + 10 + t]);
-        }
+      if (W2) {
+        // Im[b conj(T2) + c conj(A)], b = i k.mu e, c = -1/2 k.th.k e
+        const double2 R0 = term(z2.re[0], z2.im[0], 1.0), R1 = term(z2.re[1], z2.im[1], kz0),
+                      R2 = term(z2.re[2], z2.im[2], kz0 * kz0);
+        const double2 A0 = term(za.re[0], za.im[0], 1.0), A1 = term(za.re[1], za.im[1], kz0),
+                      A2 = term(za.re[2], za.im[2], kz0 * kz0), A3 = term(za.re[3], za.im[3], kz0 * kz0 * kz0);
+        const double* __restrict__ m = mu + 3 * (size_t)row;
+        const double* __restrict__ th = theta + 6 * (size_t)row;
+        const double b0 = kx * m[0] + ky * m[1], b1 = m[2];
+        const double c0 = -0.5 * (kx * kx * th[0] + ky * ky * th[3]) - kx * ky * th[1];
+        const double c1 = -(kx * th[2] + ky * th[4]), c2 = -0.5 * th[5];
+        const double zi = b0 * R0.x + b1 * R1.x + c0 * A0.y + c1 * A1.y + c2 * A2.y;
+        o[13] -= kx * zi;
+        o[14] -= ky * zi;
+        o[15] -= b0 * R1.x + b1 * R2.x + c0 * A1.y + c1 * A2.y + c2 * A3.y;
+        o[17] -= kx * R0.y;
+        o[18] -= ky * R0.y;
+        o[19] -= R1.y;
+        const double h = -0.5 * A0.x, h1 = -0.5 * A1.x;
+        o[20] += h * kx * kx;
+        o[21] += h * kx * ky;
+        o[22] += h1 * kx;
+        o[23] += h * ky * ky;
+        o[24] += h1 * ky;
+        o[25] -= 0.5 * A2.x;
       }
     }
   }
 }
 
-template <int BWD, int S>
-__global__ __launch_bounds__(256) void k_project_qm(Grid g, FrameArg fa, int n_pc, const double2* __restrict__ smm,
-                                                    size_t smm_stride, const double* __restrict__ Q,
-                                                    const double* __restrict__ mu, const double* __restrict__ theta,
-                                                    const double* __restrict__ qeff,
-                                                    const double2* __restrict__ qtab,
-                                                    const double2* __restrict__ sabc,
-                                                    const double* __restrict__ kw, int qmqm,
-                                                    double* __restrict__ qacc, double* __restrict__ det) {
-  __shared__ double red[project_lds_doubles<BWD>()];
-  const int f = blockIdx.z;
+// block -> (site tile, kind) and block `pc` of n_pc of its parts (column groups
+// x n_ks ranges of p), one part per wave
+template <int BWD, bool HS, bool QQ>
+__global__ __launch_bounds__(256, 2) void k_project_qm(Grid g, FrameArg fa, int combos, int n_pc, int n_gp, int n_ks,
+                                                      const double2* __restrict__ smm, size_t smm_stride,
+                                                      const double* __restrict__ Q, const double* __restrict__ mu,
+                                                      const double* __restrict__ theta,
+                                                      const double* __restrict__ qeff,
+                                                      const double2* __restrict__ qtab,
+                                                      const double2* __restrict__ sabc,
+                                                      const double* __restrict__ kw, double* __restrict__ qacc,
+                                                      double* __restrict__ det) {
+  // the (tile, kind) combinations of one frame's columns go to one XCD (blocks
+  // go to the 8 XCDs in turn), where they share the reads of S_MM, A, B and C
+  const int slot = blockIdx.x >> 3, combo = slot % combos, unit = (slot / combos) * 8 + (blockIdx.x & 7);
+  if (unit >= n_pc * fa.n_frames) return;
+  const int f = unit / n_pc, pc = unit - f * n_pc;
   const FrameDev fr = get_frame(fa, f);
-  project_qm_item<BWD, S>(g, fr, f, blockIdx.x, blockIdx.y, n_pc, smm, smm_stride, Q, mu, theta, qeff, qtab, sabc,
-                          kw, qmqm, qacc, det, red);
+  constexpr int KINDS = QQ ? 2 : 1;
+  const int tile = combo / KINDS, kind = combo - tile * KINDS;
+  if (16 * tile >= fr.nq) return;
+  const int lane = threadIdx.x & 63, wave = uniform_int(threadIdx.x >> 6);
+  const int part = 4 * pc + wave, gp = part / n_ks, ks = part - gp * n_ks;
+  const int groups = (g.NCOL + 15) / 16, steps = (g.mz + 4) / 4;
+  const int g0 = (int)((long)groups * gp / n_gp), g1 = (int)((long)groups * (gp + 1) / n_gp);
+  const int s0 = steps * ks / n_ks, s1 = steps * (ks + 1) / n_ks;
+  // slots of the sums this block forms, in steps of four
+  const int t0 = kind ? 12 : BWD != 1 ? 0 : 8, t1 = kind ? 26 : QQ ? 17 : BWD ? 13 : 10;
+  double o[28];
+#pragma unroll
+  for (int t = 0; t < 28; t++) o[t] = 0.0;
+  if (gp < n_gp) {
+    if (!QQ || kind == 0)
+      project_wave<BWD, HS, QQ, 0>(g, fr, f, lane, tile, g0, g1, s0, s1, smm, smm_stride, Q, mu, theta, qeff, qtab, sabc, kw, o);
+    else
+      project_wave<BWD, HS, QQ, 1>(g, fr, f, lane, tile, g0, g1, s0, s1, smm, smm_stride, Q, mu, theta, qeff, qtab, sabc, kw, o);
+  }
+  // over the four lane rows of a site (row r keeps slots 4 u + r), then over the waves
+  __shared__ double red[4][28][16];
+#pragma unroll
+  for (int v = 0; v < 28; v += 4)
+    if (v + 4 > t0 && v < t1)
+      red[wave][v + (lane >> 4)][lane & 15] = fold16(fold32(o[v], o[v + 2]), fold32(o[v + 1], o[v + 3]));
+  __syncthreads();
+  const int li = threadIdx.x & 15, j = 16 * tile + li;
+  if (j >= fr.nq) return;
+  double* qa = qacc + (size_t)(fr.qoff + j) * QA_STRIDE;
+  // partial sums of this block in deterministic mode, summed over the blocks in order afterwards
+  double* d = det ? det + ((size_t)(fr.qoff + j) * n_pc * KINDS + pc * KINDS + kind) * 26 : nullptr;
+  constexpr int first = BWD == 1 ? 10 : 0;
+  for (int t = first + (threadIdx.x >> 4); t < 26; t += 16) {
+    const bool mine = t >= t0 && t < t1 && !(kind && t == 16);
+    const double sum = mine ? red[0][t][li] + red[1][t][li] + red[2][t][li] + red[3][t][li] : 0.0;
+    if (d)
+      d[t - first] = sum;
+    else if (mine)
+      atomicAdd(&qa[t < 10 ? QA_PHI_LR + t : QA_G_QMMM_LR + t - 10], sum);
+  }
 }
 
-hipError_t launch_project_qm(const Grid& g, const FrameArg& fa, int max_nq, int total_nq, const double2* smm,
+hipError_t launch_project_qm(const Grid& g, const FrameArg& fa, int max_nq, const double2* smm,
                              size_t smm_frame_stride, const double* Q, const double* mu, const double* theta,
                              int backward, int qmqm, Work& w, hipStream_t s) {
   if (max_nq == 0) return hipSuccess;
-  // two sites per block (the per-k loads serve both); about 640 blocks in all:
-  // enough k items per thread to amortise the block reduction
-  constexpr int S = 2;
-  const int site_blocks = (total_nq + S - 1) / S;
-  int n_pc = (640 + site_blocks - 1) / (site_blocks > 0 ? site_blocks : 1);
-  const int kblocks = (g.NCOL * (g.mz + 1) + 255) / 256;
-  if (n_pc > kblocks) n_pc = kblocks;
-  if (w.det_proj && n_pc > kDetPc) n_pc = kDetPc;
-  if (n_pc < 1) n_pc = 1;
-  dim3 grid((max_nq + S - 1) / S, n_pc, fa.n_frames);
-#define PQ(B)                                                                                                  \
-  hipLaunchKernelGGL((k_project_qm<B, S>), grid, dim3(256), 0, s, g, fa, n_pc, smm, smm_frame_stride, Q, mu, \
-                     theta, w.qeff, w.qm_tab, w.sabc, w.kw, qmqm, w.qacc, w.det_proj)
-  if (backward == 2)
-    PQ(2);
-  else if (backward)
-    PQ(1);
+  const bool qq = backward && qmqm;
+  if (!smm && !qq) return hipSuccess;
+  const int kinds = qq ? 2 : 1, combos = (max_nq + 15) / 16 * kinds;
+  // about four waves per SIMD in all; where one wave per column group leaves
+  // SIMDs idle, the p range of each is split in two
+  const int groups = (g.NCOL + 15) / 16;
+  const int per = combos * fa.n_frames;
+  int n_gp = std::min(groups, (4096 / per + 4) / 4 * 4);
+  const int n_ks = n_gp * per < 1024 && g.mz >= 7 ? 2 : 1;
+  if (w.det_proj) n_gp = std::min(n_gp, 4 * kDetPc / (kinds * n_ks));
+  const int n_pc = (n_gp * n_ks + 3) / 4;
+  const dim3 grid((n_pc * fa.n_frames + 7) / 8 * 8 * combos);
+#define PQ(B, H, D)                                                                                              \
+  hipLaunchKernelGGL((k_project_qm<B, H, D>), grid, dim3(256), 0, s, g, fa, combos, n_pc, n_gp, n_ks, smm,       \
+                     smm_frame_stride, Q, mu, theta, w.qeff, w.qm_tab, w.sabc, w.kw, w.qacc, w.det_proj)
+  if (!smm)
+    PQ(1, false, true);
+  else if (!backward)
+    PQ(0, true, false);
+  else if (backward == 2 && qq)
+    PQ(2, true, true);
+  else if (backward == 2)
+    PQ(2, true, false);
+  else if (qq)
+    PQ(1, true, true);
   else
-    PQ(0);
+    PQ(1, true, false);
 #undef PQ
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !w.det_proj) return e;
@@ -1338,7 +1440,7 @@ hipError_t launch_project_qm(const Grid& g, const FrameArg& fa, int max_nq, int 
   DetMap m{};
   if (backward != 1) m = det_range(m, QA_PHI_LR, 10);
   if (backward) m = det_range(m, QA_G_QMMM_LR, 16);
-  return launch_det_reduce(fa, 1, max_nq, w.det_proj, n_pc, 26, m, w.qacc, QA_STRIDE, s);
+  return launch_det_reduce(fa, 1, max_nq, w.det_proj, n_pc * kinds, 26, m, w.qacc, QA_STRIDE, s);
 }
 
 // ------------------------------------------------------------------ MM gradients (backward hot loop)

@@ -42,6 +42,7 @@
 #include <vector>
 
 #include "ewald_internal.h"
+#include "lanes.h"
 
 namespace mpe {
 
@@ -708,24 +709,6 @@ DEV double row_sum(double v) {
   v += row_rotate<0x122>(v);
   v += row_rotate<0x121>(v);
   return v;
-}
-
-// x of the lower and y of the upper half wave, each summed over both halves
-DEV double fold32(double x, double y) {
-  const unsigned long long a = __double_as_longlong(x), b = __double_as_longlong(y);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)(a & 0xffffffffu), (unsigned)(b & 0xffffffffu), false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
-  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-
-// x of the even and y of the odd rows of 16 lanes, each summed over a row pair
-DEV double fold16(double x, double y) {
-  const unsigned long long a = __double_as_longlong(x), b = __double_as_longlong(y);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)(a & 0xffffffffu), (unsigned)(b & 0xffffffffu), false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
-  return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-         __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
 }
 
 // a tile and where its atoms sit among the sorted ones: lane r < 8 holds the
