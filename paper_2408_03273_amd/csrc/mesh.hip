@@ -660,28 +660,41 @@ __global__ __launch_bounds__(256) void k_mesh_wk(Mesh m, int KF, const double2* 
 }
 
 // ------------------------------------------------------------------ reading the mesh at the charges
-// Persistent blocks of 12 waves (one per CU) take tiles of 8 x 8 x 16 mesh
-// cells in turn.  A tile's atoms read 23 x 23 x 32 mesh points, which are
-// staged in LDS (135 KB; tiles start at cells 16 k + 8 in z, so that a row of 32
-// points is two cache lines); the next tile's points are loaded into registers
-// while this tile's atoms are evaluated.  A wave takes one atom at a time:
-// lanes 0..47 evaluate the 48 taps and their derivatives from polynomials kept
-// in registers; then lanes hold 16 z points x 4 y points (y in four rounds) and
-// the x points come one after another, their two factors read from the lanes
-// into scalar registers.  Each lane sums its column over x with both (128
-// multiply-adds for the atom's 4096 points), then the y and z factors give
-// potential and gradient, reduced over the wave.  The 4096 reads per atom
-// bound it: 32 KB per atom from LDS at 128 bytes per cycle and CU.  Three waves
-// per SIMD with the reads of one x point ahead cover each other's start and end
-// of an atom better than two with the reads of two points ahead (112^3 mesh,
-// 16 frames of 100 000 charges: 1.60 ms with 8 waves, 1.45 ms with 12; the LDS
-// reads alone 0.85 ms); a fourth wave does not fit the registers.
-static constexpr int kGatherX = 8, kGatherY = 8, kGatherZ = 16;                             // cells of a tile
-static constexpr int kGatherWX = kGatherX + 15, kGatherWY = kGatherY + 15, kGatherWZ = 32;  // staged points
-static constexpr int kGatherBlocks = 256;                                                   // one per CU
+// A block (one per CU) marches along x through columns of 8 x 16 mesh cells in
+// y and z, four cells (one bin) per step.  A step's atoms read 19 x 23 x 31 mesh
+// points; the planes live in a ring in LDS, so that a step loads only the four
+// planes it adds (24 KB per 512 cells; a tile of 1024 cells by itself reads
+// 135 KB).  27 planes let waves drift one step apart: a wave that enters step k
+// adds its share of the planes of step k + 1 (loaded into registers during step
+// k - 1) and counts itself in, then takes atoms, which the waves claim one after
+// another; it enters k + 1 once all waves have counted in for k.  A wave's share
+// of the planes of k + 1 replaces planes last read in step k - 2, which every
+// wave has left when it counts in for k - 1.
+//
+// A wave takes one atom at a time: lanes 0..47 evaluate the 48 taps and their
+// derivatives from polynomials kept in registers; then lanes hold 16 z points
+// x 4 y points (y in four rounds) and the x points come one after another,
+// their two factors read from the lanes into scalar registers.  Each lane sums
+// its column over x with both (128 multiply-adds for the atom's 4096 points),
+// then the y and z factors give potential and gradient, reduced over the wave.
+// The 4096 reads per atom bound it: 32 KB per atom from LDS at 128 bytes per
+// cycle and CU.  Three waves per SIMD with the reads of one x point ahead cover
+// each other's start and end of an atom.
+// Measured against tiles of 8 x 8 x 16 cells, each staged whole, dealt to the
+// waves in turn: 16 frames of 100 000 charges on a 112^3 mesh 1.45 -> 1.38 ms (the
+// LDS reads alone 0.85 ms), 64 frames of 5000 to 30 000 on 80^3 1.62 -> 1.09 ms,
+// one of 35 000 on 96^3 54 -> 50 us.  With 8 waves 1.64 ms and 1.23 ms, with 16
+// (registers short) 1.43 and 1.17 ms.
+static constexpr int kGatherY = 8, kGatherZ = 16;                        // cells of a column
+static constexpr int kGatherWY = kGatherY + 15, kGatherWZ = kGatherZ + 15;  // points of a plane
+static constexpr int kGatherWindow = 4 + 15;                             // planes a step reads
+static constexpr int kGatherRing = kGatherWindow + 8;                    // planes kept
+static constexpr int kGatherPlane = kGatherWY * kGatherWZ;
+static constexpr int kGatherBlocks = 256;                                // one per CU
 static constexpr int kGatherWaves = 12;
-static constexpr int kGatherRows = kGatherWX * kGatherWY;
-static constexpr int kGatherRounds = (kGatherRows + 4 * kGatherWaves - 1) / (4 * kGatherWaves);  // 16 lanes per row
+static constexpr int kGatherGroups = 4 * kGatherWaves;                   // rows loaded at a time, 16 lanes each
+static constexpr int kGatherFill = (kGatherWindow * kGatherWY + kGatherGroups - 1) / kGatherGroups;
+static constexpr int kGatherAdd = (4 * kGatherWY + kGatherGroups - 1) / kGatherGroups;
 
 typedef double v2d __attribute__((ext_vector_type(2)));
 
@@ -711,212 +724,241 @@ DEV double row_sum(double v) {
   return v;
 }
 
-// a tile and where its atoms sit among the sorted ones: lane r < 8 holds the
-// first atom (s0) and the running count (exc) of bin row r (2 in y, 4 in z;
-// two bins in x)
-struct GatherTile {
-  int f, X0, Y0, Z0, moff;
+// A step's atoms among the sorted ones: lane r < 8 holds the first atom (s0)
+// and the running count (exc) of bin row r (2 in y, 4 in z).
+struct GatherStep {
   int s0, exc, total;
 };
 
-__global__ __launch_bounds__(64 * kGatherWaves) void k_mesh_gather(Mesh m, FrameArg fa, int tx, int ty, int tz,
+__global__ __launch_bounds__(64 * kGatherWaves) void k_mesh_gather(Mesh m, FrameArg fa, int ty, int tz, int parts,
                                                       const int* __restrict__ start, const double* __restrict__ poly,
                                                       const double4* __restrict__ off, const int2* __restrict__ cell,
                                                       const double* __restrict__ mesh, double* __restrict__ fpart) {
-  __shared__ v2d win[kGatherRows * kGatherWZ / 2];
+  __shared__ double ring[kGatherRing * kGatherPlane];
   __shared__ double2 tv[kGatherWaves][32];
+  __shared__ int counted, claimed;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const int per = tx * ty * tz, tiles = per * fa.n_frames;
-  // each XCD (blocks go to the 8 XCDs in turn) takes a contiguous run of tiles
-  const int nx = min(8, (int)gridDim.x), xcd = blockIdx.x % nx;
-  const int step = ((int)gridDim.x - xcd + nx - 1) / nx;  // blocks of this XCD
-  const int t_end = (int)((long)tiles * (xcd + 1) / nx);
-  int t = (int)((long)tiles * xcd / nx) + blockIdx.x / nx;
-  if (t >= t_end) return;
-
-  auto place = [&](GatherTile& g, int tile) {
-    g.f = tile / per;
-    const int bid = tile - g.f * per;
-    const int bz = bid / (tx * ty), by = (bid - bz * tx * ty) / tx, bx = bid - (bz * ty + by) * tx;
-    g.X0 = kGatherX * bx;
-    g.Y0 = kGatherY * by;
-    g.Z0 = kGatherZ * bz - 8;  // the first z tile wraps
-    g.moff = mesh_frame(fa, g.f).moff;
-  };
-  auto rows_of = [&](const GatherTile& g) {  // first and last + 1 atom of bin row `lane`
-    int2 r = make_int2(0, 0);
-    if (lane < 8) {
-      int rz = (g.Z0 >> 2) + (lane >> 1);
-      rz += rz < 0 ? m.nb[2] : 0;
-      const int* __restrict__ st = start + (size_t)g.f * (m.nbt + 1) +
-                                   (rz * m.nb[1] + (g.Y0 >> 2) + (lane & 1)) * m.nb[0] + (g.X0 >> 2);
-      r = make_int2(st[0], st[2]);
-    }
-    return r;
-  };
-  auto count = [&](GatherTile& g, int2 r) {
-    const int len = r.y - r.x;
-    int inc = len;
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-      const int u = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += u;
-    }
-    g.s0 = r.x;
-    g.total = __builtin_amdgcn_readlane(inc, 7);
-    g.exc = lane < 8 ? inc - len : 0x7fffffff;
-  };
-  // the tile's points: 16 lanes per (x, y) row, z from Z0 - 8
-  const int grp = tid >> 4, zp = 2 * (tid & 15);
-  v2d v[kGatherRounds];
-#pragma unroll
-  for (int u = 0; u < kGatherRounds; u++) v[u] = v2d{0.0, 0.0};
-  auto load = [&](const GatherTile& g) {
-    const double* __restrict__ src = mesh + (size_t)g.f * m.N[0] * m.N[1] * m.N[2];
-    int gz = g.Z0 - 8 + zp;
-    gz += gz < 0 ? m.N[2] : gz >= m.N[2] ? -m.N[2] : 0;
-    int r0 = grp;
-    asm("" : "+v"(r0));  // (the rows' coordinates are formed anew for each tile: kept, they take 34 registers)
-#pragma unroll
-    for (int u = 0; u < kGatherRounds; u++) {
-      const int r = min(r0 + 4 * kGatherWaves * u, kGatherRows - 1);
-      const int x = r / kGatherWY, y = r - x * kGatherWY;
-      int gx = g.X0 - 7 + x, gy = g.Y0 - 7 + y;
-      gx += gx < 0 ? m.N[0] : gx >= m.N[0] ? -m.N[0] : 0;
-      gy += gy < 0 ? m.N[1] : gy >= m.N[1] ? -m.N[1] : 0;
-      v[u] = *(const v2d*)(src + (size_t)((gx * m.N[1] + gy) * m.N[2] + gz));
-    }
-  };
   const int lz = lane & 15, ly = lane >> 4;
-  const int ax = min(ly, 2), tap = lz;
+  const int grp = tid >> 4, zp = 2 * (tid & 15);
   double c[kMeshPoly];
   {
-    const double* __restrict__ pc = poly + (tap < 8 ? tap : 15 - tap) * kMeshPoly;
+    const double* __restrict__ pc = poly + (lz < 8 ? lz : 15 - lz) * kMeshPoly;
 #pragma unroll
-    for (int k = 0; k < kMeshPoly; k++) c[k] = (k & 1) && tap >= 8 ? -pc[k] : pc[k];
+    for (int k = 0; k < kMeshPoly; k++) c[k] = (k & 1) && lz >= 8 ? -pc[k] : pc[k];
   }
-  // an atom's offset along the lane's axis, its cell and its row
-  struct Atom {
-    double s;
-    int cx, row;
-  };
-  auto fetch = [&](const GatherTile& g, int j) {
-    const int row_of = (int)__popcll(__ballot(g.exc <= j)) - 1;  // the bin row that holds the tile's atom j
-    const int p = g.moff + __builtin_amdgcn_readlane(g.s0, row_of) + j - __builtin_amdgcn_readlane(g.exc, row_of);
-    Atom a;
-    a.s = ((const double*)(off + p))[ax];
-    const int2 ce = cell[p];
-    a.cx = ce.x;
-    a.row = ce.y;
-    return a;
-  };
-  auto evaluate = [&](const GatherTile& g, const Atom& at, double scale) {
-    const double s = at.s;
-    double pv = c[kMeshPoly - 1], pd = 0.0;
-#pragma unroll
-    for (int k = kMeshPoly - 2; k >= 0; k--) {
-      pd = fma(pd, s, pv);
-      pv = fma(pv, s, c[k]);
-    }
-    pd *= 2.0;  // d/dt
-    if (lane >= 16 && lane < 48) tv[wave][lane - 16] = make_double2(pv, pd);
-    const int cx = uni(at.cx);
-    int dz = (cx >> 20 & 1023) - g.Z0;
-    dz -= dz >= m.N[2] ? m.N[2] : 0;
-    const double* w0 = (const double*)win +
-                       (((cx & 1023) - g.X0) * kGatherWY + (cx >> 10 & 1023) - g.Y0 + ly) * kGatherWZ + dz + 1 + lz;
-    // the reads of the next x point are issued ahead of the multiply-adds of this one
-    double A[4] = {0.0, 0.0, 0.0, 0.0}, D[4] = {0.0, 0.0, 0.0, 0.0}, w[2][4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) w[0][q] = w0[4 * q * kGatherWZ];
-#pragma unroll
-    for (int x = 0; x < 16; x++) {
-      if (x < 15) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) w[(x + 1) & 1][q] = w0[((x + 1) * kGatherWY + 4 * q) * kGatherWZ];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      const double xv = lane_value(pv, x), xd = lane_value(pd, x);
-#pragma unroll
-      for (int q = 0; q < 4; q++) {
-        A[q] = fma(xv, w[x & 1][q], A[q]);
-        D[q] = fma(xd, w[x & 1][q], D[q]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    lds_wave_sync();
-    double u0 = 0.0, u1 = 0.0, u2 = 0.0;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const double2 y = tv[wave][ly + 4 * q];
-      u0 = fma(y.x, A[q], u0);
-      u1 = fma(y.x, D[q], u1);
-      u2 = fma(y.y, A[q], u2);
-    }
-    const double2 z = tv[wave][16 + lz];
-    lds_wave_sync();  // the taps are replaced for the next atom
-    const double o0 = u0 * z.x, o1 = u1 * z.x, o2 = u2 * z.x, o3 = u0 * z.y;
-    // four sums over 64 lanes: row ly of 16 lanes ends with o<ly>
-    const double a = row_sum(fold16(fold32(o0, o2), fold32(o1, o3)));
-    if (lz == 0) fpart[(size_t)at.row * 4 + ly] = a * scale;
-  };
+  const int ax = min(ly, 2);
 
-  GatherTile cur, nxt;
-  place(cur, t);
-  count(cur, rows_of(cur));
-  if (cur.total) load(cur);
-  Atom first2{}, next2{};  // this wave's first two atoms of the coming tile
-  if (wave < cur.total) first2 = fetch(cur, wave);
-  if (wave + kGatherWaves < cur.total) next2 = fetch(cur, wave + kGatherWaves);
-  bool more = t + step < t_end;
-  int2 nrow = make_int2(0, 0);
-  if (more) {
-    place(nxt, t + step);
-    nrow = rows_of(nxt);
-  }
-  while (true) {
-    if (cur.total) {
+  // Segments: column u / parts of a frame, part u % parts of its steps.  The
+  // 8 XCDs (blocks go to them in turn) take contiguous eighths of each frame's
+  // segments, another eighth from frame to frame (frames come largest first).
+  const int per = parts * ty * tz, xcd = blockIdx.x & 7;
+  int i = blockIdx.x >> 3;  // the block's place in its XCD's list
+  for (int f = 0; f < fa.n_frames; f++) {
+    const int e = (xcd + f) & 7, u0 = (int)((long)per * e / 8), u1 = (int)((long)per * (e + 1) / 8);
+    for (; i < u1 - u0; i += gridDim.x >> 3) {
+      const int u = u0 + i, part = u % parts, col = u / parts;
+      const int by = col % ty, bz = col / ty;
+      const int Y0 = kGatherY * by, Z0 = kGatherZ * bz - 8;  // the first column in z wraps
+      const int b0 = m.nb[0] * part / parts, len = m.nb[0] * (part + 1) / parts - b0, X0 = 4 * b0;
+      const MeshFrame fr = mesh_frame(fa, f);
+      const double* __restrict__ src = mesh + (size_t)f * m.N[0] * m.N[1] * m.N[2];
+      const int* __restrict__ st = start + (size_t)f * (m.nbt + 1);
+
+      auto rows_of = [&](int k) {  // first and last + 1 atom of the step's bin row `lane`
+        int2 r = make_int2(0, 0);
+        if (lane < 8) {
+          int rz = (Z0 >> 2) + (lane >> 1);
+          rz += rz < 0 ? m.nb[2] : 0;
+          const int* __restrict__ p = st + (rz * m.nb[1] + (Y0 >> 2) + (lane & 1)) * m.nb[0] + b0 + k;
+          r = make_int2(p[0], p[1]);
+        }
+        return r;
+      };
+      auto count = [&](int2 r) {
+        const int n = r.y - r.x;
+        int inc = n;
 #pragma unroll
-      for (int u = 0; u < kGatherRounds; u++)
-        if (grp + 4 * kGatherWaves * u < kGatherRows)
-          win[(grp + 4 * kGatherWaves * u) * (kGatherWZ / 2) + (zp >> 1)] = v[u];
-    }
-    __syncthreads();
-    // Order of the loads, which return in order: this wave's first two atoms of
-    // the next tile, the bin rows of the tile after it, the next tile's points.
-    const Atom first = first2, at1 = next2;
-    t += step;
-    GatherTile after = nxt;
-    if (more) {
-      count(nxt, nrow);
-      if (wave < nxt.total) first2 = fetch(nxt, wave);
-      if (wave + kGatherWaves < nxt.total) next2 = fetch(nxt, wave + kGatherWaves);
-      if (t + step < t_end) {
-        place(after, t + step);
-        nrow = rows_of(after);
+        for (int o = 1; o < 8; o <<= 1) {
+          const int v = __shfl_up(inc, o, 64);
+          if (lane >= o) inc += v;
+        }
+        return GatherStep{r.x, lane < 8 ? inc - n : 0x7fffffff, (int)__builtin_amdgcn_readlane(inc, 7)};
+      };
+      // points zp - 1 and zp (of 31; point 0 pairs with one outside) of row y of plane p
+      int gz = Z0 - 8 + zp;
+      gz += gz < 0 ? m.N[2] : gz >= m.N[2] ? -m.N[2] : 0;
+      auto load = [&](int p, int y) {
+        int gx = X0 - 7 + p, gy = Y0 - 7 + y;
+        gx += gx < 0 ? m.N[0] : gx >= m.N[0] ? -m.N[0] : 0;
+        gy += gy < 0 ? m.N[1] : gy >= m.N[1] ? -m.N[1] : 0;
+        return *(const v2d*)(src + (size_t)((gx * m.N[1] + gy) * m.N[2] + gz));
+      };
+      auto put = [&](int slot, int y, v2d v) {
+        double* d = ring + slot * kGatherPlane + y * kGatherWZ + zp - 1;
+        if (zp) d[0] = v.x;
+        d[1] = v.y;
+      };
+
+      __syncthreads();  // the previous segment has been read
+      if (tid == 0) counted = claimed = 0;
+      {
+        v2d v[kGatherFill];
+#pragma unroll
+        for (int t = 0; t < kGatherFill; t++) {
+          const int r = min(grp + kGatherGroups * t, kGatherWindow * kGatherWY - 1), p = r / kGatherWY;
+          v[t] = load(p, r - p * kGatherWY);
+        }
+#pragma unroll
+        for (int t = 0; t < kGatherFill; t++) {
+          const int r = grp + kGatherGroups * t, p = r / kGatherWY;
+          if (r < kGatherWindow * kGatherWY) put(p, r - p * kGatherWY, v[t]);
+        }
       }
-      if (nxt.total) load(nxt);
-    }
-    const MeshFrame fr = mesh_frame(fa, cur.f);
-    // group ly ends with the potential (0) or a gradient component (per mesh cell -> per length)
-    const double scale = ly == 0   ? 1.0
-                         : ly == 1 ? m.N[0] * fr.inv_box[0]
-                         : ly == 2 ? m.N[1] * fr.inv_box[1]
-                                   : m.N[2] * fr.inv_box[2];
-    if (wave < cur.total) {
-      Atom next = at1;
-      evaluate(cur, first, scale);
-      for (int j = wave + kGatherWaves; j < cur.total; j += kGatherWaves) {
-        const Atom at = next;
-        if (j + kGatherWaves < cur.total) next = fetch(cur, j + kGatherWaves);
-        evaluate(cur, at, scale);
+      v2d add[kGatherAdd];
+      auto load_step = [&](int k) {  // the planes step k adds
+#pragma unroll
+        for (int t = 0; t < kGatherAdd; t++) {
+          const int r = min(grp + kGatherGroups * t, 4 * kGatherWY - 1), p = r / kGatherWY;
+          add[t] = load(kGatherWindow - 4 + 4 * k + p, r - p * kGatherWY);
+        }
+      };
+      auto put_step = [&](int k) {
+        const int s = (kGatherWindow - 4 + 4 * k) % kGatherRing;
+#pragma unroll
+        for (int t = 0; t < kGatherAdd; t++) {
+          const int r = grp + kGatherGroups * t, p = r / kGatherWY;
+          if (r < 4 * kGatherWY) put(s + p >= kGatherRing ? s + p - kGatherRing : s + p, r - p * kGatherWY, add[t]);
+        }
+      };
+
+      // Waves claim the segment's atoms in order, each claim on its way while
+      // the wave works on the atoms claimed before.  The claim `j` counts from the
+      // first atom of step kf.
+      int kf = 0, base = 0, next = 0;
+      GatherStep g = count(rows_of(0));
+      int2 ahead = rows_of(min(1, len - 1));
+      auto claim = [&]() {
+        next = 0;
+        if (lane == 0) next = __hip_atomic_fetch_add(&claimed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      };
+      // an atom's step (len: no more atoms), its offset along the lane's axis, its cell and its row
+      struct Atom {
+        double s;
+        int k, cx, row;
+      };
+      auto fetch = [&]() {
+        Atom a{};
+        const int j = uni(next);
+        while (j - base >= g.total && kf < len) {
+          base += g.total;
+          kf++;
+          g = count(ahead);
+          ahead = rows_of(min(kf + 1, len - 1));
+        }
+        a.k = kf;
+        if (kf < len) {
+          claim();
+          const int jf = j - base;
+          const int row = (int)__popcll(__ballot(g.exc <= jf)) - 1;  // the bin row that holds the atom
+          const int p = fr.moff + __builtin_amdgcn_readlane(g.s0, row) + jf - __builtin_amdgcn_readlane(g.exc, row);
+          a.s = ((const double*)(off + p))[ax];
+          const int2 ce = cell[p];
+          a.cx = ce.x;
+          a.row = ce.y;
+        }
+        return a;
+      };
+      // group ly ends with the potential (0) or a gradient component (per mesh cell -> per length)
+      const double scale = ly == 0   ? 1.0
+                           : ly == 1 ? m.N[0] * fr.inv_box[0]
+                           : ly == 2 ? m.N[1] * fr.inv_box[1]
+                                     : m.N[2] * fr.inv_box[2];
+      auto evaluate = [&](const Atom& at) {
+        const double s = at.s;
+        double pv = c[kMeshPoly - 1], pd = 0.0;
+#pragma unroll
+        for (int k = kMeshPoly - 2; k >= 0; k--) {
+          pd = fma(pd, s, pv);
+          pv = fma(pv, s, c[k]);
+        }
+        pd *= 2.0;  // d/dt
+        if (lane >= 16 && lane < 48) tv[wave][lane - 16] = make_double2(pv, pd);
+        const int cx = uni(at.cx);
+        int dz = (cx >> 20 & 1023) - Z0;
+        dz -= dz >= m.N[2] ? m.N[2] : 0;
+        const double* w0 = ring + ((cx >> 10 & 1023) - Y0 + ly) * kGatherWZ + dz + lz;
+        const int slot = ((cx & 1023) - X0) % kGatherRing;  // of the atom's first plane
+        auto plane = [&](int x) { return w0 + (slot + x >= kGatherRing ? slot + x - kGatherRing : slot + x) * kGatherPlane; };
+        // the reads of the next x point are issued ahead of the multiply-adds of this one
+        double A[4] = {0.0, 0.0, 0.0, 0.0}, D[4] = {0.0, 0.0, 0.0, 0.0}, w[2][4];
+        const double* wp = plane(0);
+#pragma unroll
+        for (int q = 0; q < 4; q++) w[0][q] = wp[4 * q * kGatherWZ];
+#pragma unroll
+        for (int x = 0; x < 16; x++) {
+          if (x < 15) {
+            wp = plane(x + 1);
+#pragma unroll
+            for (int q = 0; q < 4; q++) w[(x + 1) & 1][q] = wp[4 * q * kGatherWZ];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          const double xv = lane_value(pv, x), xd = lane_value(pd, x);
+#pragma unroll
+          for (int q = 0; q < 4; q++) {
+            A[q] = fma(xv, w[x & 1][q], A[q]);
+            D[q] = fma(xd, w[x & 1][q], D[q]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_wave_sync();
+        double u0 = 0.0, u1 = 0.0, u2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const double2 y = tv[wave][ly + 4 * q];
+          u0 = fma(y.x, A[q], u0);
+          u1 = fma(y.x, D[q], u1);
+          u2 = fma(y.y, A[q], u2);
+        }
+        const double2 z = tv[wave][16 + lz];
+        lds_wave_sync();  // the taps are replaced for the next atom
+        const double o0 = u0 * z.x, o1 = u1 * z.x, o2 = u2 * z.x, o3 = u0 * z.y;
+        // four sums over 64 lanes: row ly of 16 lanes ends with o<ly>
+        const double a = row_sum(fold16(fold32(o0, o2), fold32(o1, o3)));
+        if (lz == 0) fpart[(size_t)at.row * 4 + ly] = a * scale;
+      };
+
+      if (len > 1) load_step(1);
+      __syncthreads();
+      claim();
+      Atom a0 = fetch(), a1 = fetch();
+      auto enter = [&](int k) {
+        // every wave counts in once per step, whether it has atoms or not, and
+        // waits only for counts of the step before: all of them come
+        if (k > 0)
+          while (__hip_atomic_load(&counted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < k * kGatherWaves)
+            __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        if (k + 1 < len) {
+          put_step(k + 1);
+          // (LDS operations of a wave take effect in order: the count follows the points)
+          asm volatile("" ::: "memory");
+          if (lane == 0) __hip_atomic_fetch_add(&counted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (k + 2 < len) load_step(k + 2);
+        }
+      };
+      enter(0);
+      int k = 0;
+      while (true) {
+        const int until = min(a0.k, len - 1);
+        while (k < until) enter(++k);
+        if (a0.k >= len) break;
+        const Atom a = a0;
+        a0 = a1;
+        a1 = fetch();
+        evaluate(a);
       }
     }
-    if (!more) return;
-    __syncthreads();  // the staged points are replaced
-    cur = nxt;
-    nxt = after;
-    more = t + step < t_end;
+    i -= u1 - u0;
   }
 }
 
@@ -990,8 +1032,21 @@ hipError_t launch_mesh_force(const Mesh& m, const Grid& g, const FrameArg& fa, i
   MCHK(left(w.mesh_btab[0], w.mesh_bt, w.mesh_bg, m.N[0], m.C[0], m.C[1] * m.C[2], F, s));
   MCHK(left(w.mesh_btab[1], w.mesh_bg, w.mesh_bh, m.N[1], m.C[1], m.C[2], F * m.N[0], s));
   MCHK(right(w.mesh_btab[2], w.mesh_bh, w.mesh_v, m.N[0] * m.N[1], m.C[2], m.N[2], F, s));
-  const int tx = m.N[0] / kGatherX, ty = m.N[1] / kGatherY, tz = m.N[2] / kGatherZ;
-  hipLaunchKernelGGL(k_mesh_gather, dim3(std::min(tx * ty * tz * F, kGatherBlocks)), dim3(64 * kGatherWaves), 0, s, m, fa, tx, ty, tz, w.mesh_start,
+  // Parts of a column's steps: the blocks' largest share, a segment's start
+  // counted as 1.5 steps.
+  const int ty = m.N[1] / kGatherY, tz = m.N[2] / kGatherZ;
+  int parts = 1;
+  double least = 1e300;
+  for (int p = 1; p <= m.nb[0]; p++) {
+    const long units = (long)p * ty * tz * F;
+    const double cost = (double)((units + kGatherBlocks - 1) / kGatherBlocks) * ((m.nb[0] + p - 1) / p + 1.5);
+    if (cost < least) {
+      least = cost;
+      parts = p;
+    }
+  }
+  const int blocks = (int)std::min((long)kGatherBlocks, ((long)parts * ty * tz * F + 7) / 8 * 8);
+  hipLaunchKernelGGL(k_mesh_gather, dim3(blocks), dim3(64 * kGatherWaves), 0, s, m, fa, ty, tz, parts, w.mesh_start,
                      w.mesh_poly, w.mesh_off, w.mesh_cell, w.mesh_v, w.fpart);
   return hipGetLastError();
 }
