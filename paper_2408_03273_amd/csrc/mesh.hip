@@ -252,31 +252,38 @@ __global__ __launch_bounds__(256) void k_mesh_sort(Mesh m, FrameArg fa, const do
 // block owns a 16 x 8 x 16 tile, each of its four waves a 16 x 4 x 8 part as
 // two matrix-core accumulators: D[x][yz] += A[x][atom] B[atom][yz], four atoms
 // per instruction, A = q phi_x and B = phi_y phi_z.  The atoms of the bins
-// around the tile are staged in LDS 64 at a time with zeros on both sides of
+// around the tile are staged in LDS 32 at a time with zeros on both sides of
 // their taps, so that a point off the support reads a zero without a test
-// (the next 64 are on their way from memory meanwhile); each wave lists the
+// (the next 32 are on their way from memory meanwhile); each wave lists the
 // atoms whose 16^3 points meet its part, with the three LDS byte addresses of
 // its first point.  The products phi_y phi_z of a step are formed before it, so
-// that its four matrix instructions follow each other (16 frames of 100 000
-// charges on a 112^3 mesh: 1.78 ms with the products between them, 1.67 ms so;
-// the matrix cores alone 0.59 ms).  Operand reads from LDS and the matrix cores bound it about
-// equally: a 4 x 4 part has less work outside the support (31 19 19 / 16^3 =
-// 2.7 times the useful multiply-adds, 3.3 here) but twice the x reads.
+// that its two matrix instructions follow each other.  A 4 x 4 part has less work
+// outside the support (31 19 19 / 16^3 = 2.7 times the useful multiply-adds,
+// 3.3 here) but twice the x reads.  Matrix cores and LDS are each busy about
+// half the time; 27 KB of LDS and 80 registers let six blocks share a CU and cover
+// each other's staging: 16 frames of 100 000 charges on a 112^3 mesh 1.67 ms with
+// chunks of 64 and three blocks, 1.37 ms so (matrix instructions alone 0.59 ms); 64
+// frames of 5000 to 30 000 on 80^3 1.13 -> 0.90 ms.  Where the tiles are too few for
+// six blocks per CU, KS shares of the atoms per block (each with its own
+// staging, summed in LDS at the end): one frame of 35 000 on 96^3 60 us with one
+// share, 49 with two, 53 with four; one of 19 200 on 64^3 81, 58 and 47 us.
 // A staged atom: [15 zeros | x taps | 15 zeros | y taps | 7 zeros | z taps], each
 // run of zeros (and the next atom's first one) padding the taps on both sides;
 // an odd number of doubles for the LDS banks.
 static constexpr int kSpreadX = 15, kSpreadY = kSpreadX + 16 + 15, kSpreadZ = kSpreadY + 16 + 7;
 static constexpr int kSpreadAtom = kSpreadZ + 16;
 static constexpr int kSpreadTail = 16;                                  // zeros after the last atom
+static constexpr int kSpreadChunk = 32;                                  // atoms staged at a time
 static constexpr int kSpreadRows = 48;                                  // rows of bins around a tile
 
-__global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx, int ty, int tz,
+template <int KS>
+__global__ __launch_bounds__(256 * KS, KS == 4 ? 4 : 6) void k_mesh_spread(Mesh m, FrameArg fa, int tx, int ty, int tz,
                                                      const int* __restrict__ start, const double* __restrict__ taps,
                                                      const int2* __restrict__ cell, double* __restrict__ mesh) {
-  __shared__ double tp[64 * kSpreadAtom + kSpreadTail];
-  __shared__ int pk[64];
-  __shared__ int src[256];
-  __shared__ int4 list[4][64 + 24];
+  __shared__ double staged[KS][kSpreadChunk * kSpreadAtom + kSpreadTail];
+  __shared__ int cells[KS][kSpreadChunk];
+  __shared__ int sources[KS][256];
+  __shared__ int4 list[4 * KS][kSpreadChunk + 12];
   __shared__ int row_off[kSpreadRows + 1], row_s0[kSpreadRows], row_l0[kSpreadRows], row_s1[kSpreadRows];
   const int f = blockIdx.y;
   const MeshFrame fr = mesh_frame(fa, f);
@@ -284,11 +291,13 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
   const int bid = xcd_order(blockIdx.x, nt);
   const int bz = bid / (tx * ty), by = (bid - bz * tx * ty) / tx, bx = bid - (bz * ty + by) * tx;
   const int X0 = 16 * bx, Y0 = 8 * by, Z0 = 16 * bz;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int share = KS == 1 ? 0 : uni((int)(threadIdx.x >> 8)), tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
+  double* tp = staged[share];
+  int *pk = cells[share], *src = sources[share];
   const int* __restrict__ st = start + (size_t)f * (m.nbt + 1);
   // the rows of bins (6 in y, 8 in z; 8 bins along x, in two runs where they
   // wrap) whose atoms can reach the tile
-  if (wave == 0) {
+  if (threadIdx.x < 64) {
     int s0 = 0, l0 = 0, s1 = 0, len = 0;
     if (lane < kSpreadRows) {
       int ry = (Y0 >> 2) - 2 + lane % 6, rz = (Z0 >> 2) - 2 + lane / 6;
@@ -320,21 +329,29 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
     }
     if (lane == 0) row_off[0] = 0;
   }
-  for (int e = tid; e < 64 * kSpreadAtom + kSpreadTail; e += 256) tp[e] = 0.0;
+  for (int e = tid; e < kSpreadChunk * kSpreadAtom + kSpreadTail; e += 256) tp[e] = 0.0;
   __syncthreads();
-  const int total = row_off[kSpreadRows];
+  // chunk q holds the atoms q, q + chunks, q + 2 chunks, ...: a sample of the whole
+  // neighbourhood, so that the four parts get about as many atoms of it each; the
+  // block's shares take the chunks in turn
+  const int all = uni(row_off[kSpreadRows]), chunks = (all + kSpreadChunk - 1) / kSpreadChunk;
+  const int rounds = (chunks + KS - 1) / KS;
+  const int least = all / max(chunks, 1), more = all - least * chunks;
+  auto held = [&](int t) {  // atoms in this share's chunk t
+    const int q = share + KS * t;
+    return q < chunks ? least + (q < more) : 0;
+  };
   const int oy = 4 * (wave & 1), oz = 8 * (wave >> 1);
   const int li = lane & 15, lk = lane >> 4;
   // this lane's point relative to the wave's first one, in bytes
   const int xq = 8 * li, yq = 8 * (li >> 2), zq = 8 * (li & 3);
-  v4d acc[2][2];
-#pragma unroll
-  for (int u = 0; u < 2; u++) acc[u][0] = acc[u][1] = v4d{0.0, 0.0, 0.0, 0.0};
-  // sorted positions of 256 atoms from `base`, one per thread: the last row
-  // that starts at or before the atom
-  auto locate = [&](int base) {
-    const int j = base + tid;
-    if (j < total) {
+  v4d acc[2];
+  acc[0] = acc[1] = v4d{0.0, 0.0, 0.0, 0.0};
+  // sorted positions of the atoms of 8 chunks from t, one per thread: the last
+  // row that starts at or before the atom
+  auto locate = [&](int t) {
+    const int q = share + KS * (t + (tid >> 5)), j = q + (tid & 31) * chunks;
+    if (q < chunks && j < all) {
       int lo = 0, hi = kSpreadRows - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -344,57 +361,50 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
       src[tid] = e < row_l0[lo] ? row_s0[lo] + e : row_s1[lo] + e - row_l0[lo];
     }
   };
-  // staging: eight threads per atom load its taps (16 bytes each per axis),
-  // the atoms tid / 8 and tid / 8 + 32 of the chunk
+  // staging: eight threads per atom load its taps (16 bytes each per axis)
   const int sa = tid >> 3, sp = tid & 7;
-  double2 v[6];
-  int c[2];
-  auto load = [&](int base) {
-#pragma unroll
-    for (int h = 0; h < 2; h++)
-      if (base + sa + 32 * h < total) {
-        const size_t p = (size_t)fr.moff + src[((base & 255) + sa + 32 * h)];
-        const double2* __restrict__ from = (const double2*)(taps + p * 48) + sp;
-#pragma unroll
-        for (int ax = 0; ax < 3; ax++) v[3 * h + ax] = from[8 * ax];
-        if (sp == 0) c[h] = cell[p].x;
-      }
+  double2 vx, vy, vz;
+  int c;
+  auto load = [&](int t) {
+    if (sa < held(t)) {
+      const size_t p = (size_t)fr.moff + src[(t & 7) * kSpreadChunk + sa];
+      const double2* __restrict__ from = (const double2*)(taps + p * 48) + sp;
+      vx = from[0];
+      vy = from[8];
+      vz = from[16];
+      if (sp == 0) c = cell[p].x;
+    }
   };
-  if (total > 0) {
+  if (rounds > 0) {
     locate(0);
     __syncthreads();
     load(0);
   }
-  for (int base = 0; base < total; base += 64) {
-    const int n = min(64, total - base);
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-      const int a = sa + 32 * h;
-      if (a < n) {
-        double* d = tp + a * kSpreadAtom + 2 * sp;
-        d[kSpreadX] = v[3 * h].x;
-        d[kSpreadX + 1] = v[3 * h].y;
-        d[kSpreadY] = v[3 * h + 1].x;
-        d[kSpreadY + 1] = v[3 * h + 1].y;
-        d[kSpreadZ] = v[3 * h + 2].x;
-        d[kSpreadZ + 1] = v[3 * h + 2].y;
-        if (sp == 0) {
-          // mesh cell of the atom relative to the tile, biased by 9
-          int rx = (c[h] & 1023) - X0, ry = ((c[h] >> 10) & 1023) - Y0, rz = ((c[h] >> 20) & 1023) - Z0;
-          rx += rx < -8 ? m.N[0] : rx >= m.N[0] - 8 ? -m.N[0] : 0;
-          ry += ry < -8 ? m.N[1] : ry >= m.N[1] - 8 ? -m.N[1] : 0;
-          rz += rz < -8 ? m.N[2] : rz >= m.N[2] - 8 ? -m.N[2] : 0;
-          pk[a] = (min(rx, 60) + 9) | (min(ry, 60) + 9) << 8 | (min(rz, 60) + 9) << 16;
-        }
+  for (int t = 0; t < rounds; t++) {
+    const int n = held(t);
+    if (sa < n) {
+      double* d = tp + sa * kSpreadAtom + 2 * sp;
+      d[kSpreadX] = vx.x;
+      d[kSpreadX + 1] = vx.y;
+      d[kSpreadY] = vy.x;
+      d[kSpreadY + 1] = vy.y;
+      d[kSpreadZ] = vz.x;
+      d[kSpreadZ + 1] = vz.y;
+      if (sp == 0) {
+        // mesh cell of the atom relative to the tile, biased by 9
+        int rx = (c & 1023) - X0, ry = ((c >> 10) & 1023) - Y0, rz = ((c >> 20) & 1023) - Z0;
+        rx += rx < -8 ? m.N[0] : rx >= m.N[0] - 8 ? -m.N[0] : 0;
+        ry += ry < -8 ? m.N[1] : ry >= m.N[1] - 8 ? -m.N[1] : 0;
+        rz += rz < -8 ? m.N[2] : rz >= m.N[2] - 8 ? -m.N[2] : 0;
+        pk[sa] = (min(rx, 60) + 9) | (min(ry, 60) + 9) << 8 | (min(rz, 60) + 9) << 16;
       }
     }
     __syncthreads();
-    const int next = base + 64;
-    if ((next & 255) == 0 && next < total) {  // block-uniform
-      locate(next);  // (the positions of the previous 256 atoms were read before the barrier)
+    if (((t + 1) & 7) == 0 && t + 1 < rounds) {  // block-uniform
+      locate(t + 1);  // (the positions of the previous chunks were read before the barrier)
       __syncthreads();
     }
-    load(next);
+    if (t + 1 < rounds) load(t + 1);
     {
       bool hit = false;
       int4 ad = make_int4(0, 0, 0, 0);
@@ -409,54 +419,54 @@ __global__ __launch_bounds__(256) void k_mesh_spread(Mesh m, FrameArg fa, int tx
       }
       const unsigned long long mask = __ballot(hit);
       const int cnt = (int)__popcll(mask);
-      int4* lw = list[wave];
+      int4* lw = list[4 * share + wave];
       if (hit) lw[__popcll(mask & ((1ull << lane) - 1ull))] = ad;
       // padding to whole steps and for the reads ahead: the zeros at the end
-      if (lane < 24) lw[cnt + lane] = make_int4(512 * kSpreadAtom, 512 * kSpreadAtom, 512 * kSpreadAtom, 0);
+      if (lane < 12) lw[cnt + lane] = make_int4(8 * kSpreadChunk * kSpreadAtom, 8 * kSpreadChunk * kSpreadAtom, 8 * kSpreadChunk * kSpreadAtom, 0);
       lds_wave_sync();
-      // two groups of four atoms per step: the operands of the next step are read and
-      // the list entries of the one after while this step is contracted
+      // four atoms per step: the operands of the next step are read and the list
+      // entries of the one after while this step is contracted
       const char* __restrict__ tb = (const char*)tp;
       auto at = [&](int byte, int u) { return ((const double*)(tb + byte))[u]; };
-      int4 e0 = lw[lk], e1 = lw[4 + lk];
-      double x0 = at(e0.x + xq, 0), x1 = at(e1.x + xq, 0);
-      double p[4];
+      int4 e = lw[lk];
+      double x = at(e.x + xq, 0), p0, p1;
       {
-        const double y0 = at(e0.y + yq, 0), y1 = at(e1.y + yq, 0);
-        p[0] = y0 * at(e0.z + zq, 0);
-        p[1] = y0 * at(e0.z + zq, 4);
-        p[2] = y1 * at(e1.z + zq, 0);
-        p[3] = y1 * at(e1.z + zq, 4);
+        const double y = at(e.y + yq, 0);
+        p0 = y * at(e.z + zq, 0);
+        p1 = y * at(e.z + zq, 4);
       }
-      e0 = lw[8 + lk];
-      e1 = lw[12 + lk];
-      for (int s = 0; s < cnt; s += 8) {
-        const double n0[4] = {at(e0.x + xq, 0), at(e0.y + yq, 0), at(e0.z + zq, 0), at(e0.z + zq, 4)};
-        const double n1[4] = {at(e1.x + xq, 0), at(e1.y + yq, 0), at(e1.z + zq, 0), at(e1.z + zq, 4)};
-        e0 = lw[s + 16 + lk];
-        e1 = lw[s + 20 + lk];
+      e = lw[4 + lk];
+      for (int s = 0; s < cnt; s += 4) {
+        const double nx = at(e.x + xq, 0), ny = at(e.y + yq, 0), nz0 = at(e.z + zq, 0), nz1 = at(e.z + zq, 4);
+        e = lw[s + 8 + lk];
         __builtin_amdgcn_sched_barrier(0);
-        acc[0][0] = mfma(x0, p[0], acc[0][0]);
-        acc[0][1] = mfma(x0, p[1], acc[0][1]);
-        acc[1][0] = mfma(x1, p[2], acc[1][0]);
-        acc[1][1] = mfma(x1, p[3], acc[1][1]);
+        acc[0] = mfma(x, p0, acc[0]);
+        acc[1] = mfma(x, p1, acc[1]);
         __builtin_amdgcn_sched_barrier(0);
-        x0 = n0[0];
-        x1 = n1[0];
-        p[0] = n0[1] * n0[2];
-        p[1] = n0[1] * n0[3];
-        p[2] = n1[1] * n1[2];
-        p[3] = n1[1] * n1[3];
+        x = nx;
+        p0 = ny * nz0;
+        p1 = ny * nz1;
       }
     }
     __syncthreads();  // the staged atoms are replaced
+  }
+  if (KS > 1) {  // the shares' sums (the staged atoms have been read)
+    if (share > 0)
+#pragma unroll
+      for (int r = 0; r < 8; r++) tp[r * 256 + tid] = acc[r & 1][r >> 1];
+    __syncthreads();
+    if (share > 0) return;
+#pragma unroll
+    for (int h = 1; h < KS; h++)
+#pragma unroll
+      for (int r = 0; r < 8; r++) acc[r & 1][r >> 1] += staged[h][r * 256 + tid];
   }
   double* __restrict__ o = mesh + (((size_t)f * m.N[0] + X0) * m.N[1] + Y0 + oy + (li >> 2)) * m.N[2] + Z0 + oz + (li & 3);
   const size_t plane = (size_t)m.N[1] * m.N[2];
 #pragma unroll
   for (int r = 0; r < 4; r++)
 #pragma unroll
-    for (int u = 0; u < 2; u++) o[(size_t)(lk + 4 * r) * plane + 4 * u] = acc[0][u][r] + acc[1][u][r];
+    for (int u = 0; u < 2; u++) o[(size_t)(lk + 4 * r) * plane + 4 * u] = acc[u][r];
 }
 
 // ------------------------------------------------------------------ axis contractions
@@ -1007,8 +1017,19 @@ hipError_t launch_mesh_sort(const Mesh& m, const FrameArg& fa, int max_nm, int c
 hipError_t launch_mesh_sfac(const Mesh& m, const FrameArg& fa, Work& w, hipStream_t s) {
   const int F = fa.n_frames;
   const int tx = m.N[0] / 16, ty = m.N[1] / 8, tz = m.N[2] / 16;
-  hipLaunchKernelGGL(k_mesh_spread, dim3(tx * ty * tz, F), dim3(256), 0, s, m, fa, tx, ty, tz, w.mesh_start,
-                     w.mesh_taps, w.mesh_cell, w.mesh_q);
+  // shares of a tile's atoms: as many as the 24 waves of each CU hold at once
+  // (times of each beside the kernel)
+  const int tiles = tx * ty * tz * F;
+#define SPREAD(KS)                                                                                               \
+  hipLaunchKernelGGL(k_mesh_spread<KS>, dim3(tx * ty * tz, F), dim3(256 * KS), 0, s, m, fa, tx, ty, tz,          \
+                     w.mesh_start, w.mesh_taps, w.mesh_cell, w.mesh_q)
+  if (tiles <= 256)
+    SPREAD(4);
+  else if (tiles <= 768)
+    SPREAD(2);
+  else
+    SPREAD(1);
+#undef SPREAD
   MCHK(hipGetLastError());
   MCHK(right(w.mesh_tab[2], w.mesh_q, w.mesh_h, m.N[0] * m.N[1], m.N[2], m.C[2], F, s));
   MCHK(left(w.mesh_tab[1], w.mesh_h, w.mesh_g, m.C[1], m.N[1], m.C[2], F * m.N[0], s));
