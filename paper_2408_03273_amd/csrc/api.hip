@@ -67,7 +67,7 @@ struct ewald_plan {
   // second stream for the adjoint chain that runs beside the forward chain,
   // third for a single frame's all-pairs real space (from the start)
   hipStream_t aux = nullptr, gaux = nullptr, aux2 = nullptr, gaux2 = nullptr;
-  int serial = 0;  // run the adjoint chain on the caller's stream (isolated kernel timings)
+  int serial = -1;  // forward+backward on the caller's stream alone: 1 always, 0 no single frame, -1 by size
   int batch_serial = -1;  // batches on one stream: 1 always, 0 never, -1 by the adjoint's weight size
   int batch_target = 16384;  // matrix-core forward of a batch: blocks its atom chunking aims for
   hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_join2 = nullptr;
@@ -594,15 +594,39 @@ ewald_status_t seq_forward_tail(const Seq& q, const double* Q, const double* mu,
 }
 
 ewald_status_t fork_to(ewald_plan* pl, hipStream_t from, hipStream_t to) {
+  if (from == to) return EWALD_OK;
   HIPCHK(hipEventRecord(pl->ev_fork, from));
   HIPCHK(hipStreamWaitEvent(to, pl->ev_fork, 0));
   return EWALD_OK;
 }
 
 ewald_status_t join_to(ewald_plan* pl, hipStream_t from, hipStream_t to) {
+  if (from == to) return EWALD_OK;
   HIPCHK(hipEventRecord(pl->ev_join, from));
   HIPCHK(hipStreamWaitEvent(to, pl->ev_join, 0));
   return EWALD_OK;
+}
+
+// Whether a single frame's forward+backward sequence runs on the caller's stream
+// alone.  Two more streams let real space and the two hot loops share the GPU but
+// cost five events and as many waits: calls back to back take 300 us or more with
+// them, however small.  Crossing points, one stream against three, back to back
+// (in brackets: each call waited for):
+//   dense FP64, 19 200 atoms: kmax 16 228 against 309 us (267, 323), kmax 20
+//   300 against 326 (343, 336), kmax 24 381 against 347; 100 000 at kmax 12
+//   368 against 343; FP32 sums, 35 000: kmax 20 300 against 329 (349, 348),
+//   kmax 24 387 against 356;
+//   gridded: 35 000 on 96^3 263 against 319 (306, 325), 50 000 on 64^3 290
+//   against 336 (335, 339), on 96^3 301 against 325 (345, 332), 70 000 on 64^3 331
+//   against 330;
+//   real space over many pairs: 40 sites x 35 000 atoms 245 against 343 (296,
+//   346), 400 x 5000 270 against 345 (330, 357), 200 x 19 200 with half the box
+//   in reach 532 against 453, 80 x 60 000 with all of it 442 against 384.
+bool frame_one_stream(const ewald_plan* pl, const Seq& q) {
+  if ((double)q.max_nq * q.max_nm > 2.5e6) return false;
+  const Mesh& m = pl->mesh;
+  if (q.mesh) return q.max_nm + (double)m.N[0] * m.N[1] * m.N[2] / 60.0 < 55000.0;
+  return (double)q.max_nm * pl->g.KF < (pl->t.fp32r ? 1.3e9 : 6.5e8);
 }
 
 // Forward pass and the gradients of E (upstream gradient 1) in one sequence.
@@ -619,6 +643,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
   Work& w = pl->w;
   const Grid& g = pl->g;
   const int tables = q.mesh ? 0 : mm_tables_for(pl);
+  const bool overlap = aux != q.s;  // (aux2 differs as well, or neither)
   // positions, charge sums, cleared accumulators, unit effective moments
   ewald_status_t st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, tables, 1, PREP_POS);
   if (st != EWALD_OK) return st;
@@ -637,7 +662,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
     const Seq& q_ = qr;
     {
       const Seq& q = q_;
-      HIPCHK(hipStreamWaitEvent(q.s, pl->ev_fork, 0));
+      if (overlap) HIPCHK(hipStreamWaitEvent(q.s, pl->ev_fork, 0));
       LCHK(launch_real_qm(g, q.fa, q.max_nq, q.max_nm, pl->cap_qm, pl->cap_mm, 2, q.fp32, w, q.s, w.rpart,
                           q.mm_groups));
     }
@@ -659,7 +684,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
       LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm,
                        pl->cap_mm, tables, 1, PREP_QM_TAB));
       LCHK(launch_sfac_qm(g, q.fa, q.max_nq, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, w, q.s));
-      HIPCHK(hipEventRecord(pl->ev_qside, q.s));
+      if (overlap) HIPCHK(hipEventRecord(pl->ev_qside, q.s));
     }
   }
   // caller stream: MM phase tables and, for a single frame, the (small)
@@ -672,7 +697,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
   else
     LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm, pl->cap_mm,
                      tables, 1, PREP_MM_TAB));
-  HIPCHK(hipEventRecord(pl->ev_mtab, q.s));
+  if (overlap) HIPCHK(hipEventRecord(pl->ev_mtab, q.s));
   if (qq_first && q.qmqm && q.max_nq > 0) LCHK(launch_qmqm(g, q.fa, q.max_nq, pl->cap_qm, Q, mu, theta, w, q.s));
   // caller stream: the forward hot loop (with many frames after the QM side,
   // whose structure factors the adjoint needs: a forward grid beside them
@@ -690,7 +715,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
       // second stream: the adjoint hot loop, then real space (forward, QM-
       // and MM-side adjoint in one pass), which runs beside the projection on
       // the caller stream and is needed only by the final epilogue
-      HIPCHK(hipStreamWaitEvent(q.s, pl->ev_mtab, 0));
+      if (overlap) HIPCHK(hipStreamWaitEvent(q.s, pl->ev_mtab, 0));
       if (q.mesh)
         LCHK(launch_mesh_force(pl->mesh, g, q.fa, q.max_nm, w, q.s));
       else
@@ -709,13 +734,13 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
         LCHK(launch_qmqm(g, q.fa, q.max_nq, pl->cap_qm, Q, mu, theta, w, q.s));
     }
   }
-  HIPCHK(hipStreamWaitEvent(q.s, pl->ev_qside, 0));
+  if (overlap) HIPCHK(hipStreamWaitEvent(q.s, pl->ev_qside, 0));
   // the adjoint sums of the QM-side projection ride along with the forward ones
   st = seq_forward_tail(q, Q, mu, theta, smm, smm_stride, energy, phi, efield, efgrad, site, 1, 1, 0);
   if (st != EWALD_OK) return st;
   st = join_to(pl, aux, q.s);
   if (st != EWALD_OK) return st;
-  if (real_early && aux2 != q.s) {
+  if (real_early && overlap) {
     HIPCHK(hipEventRecord(pl->ev_join2, aux2));
     HIPCHK(hipStreamWaitEvent(q.s, pl->ev_join2, 0));
   }
@@ -782,8 +807,8 @@ ewald_status_t ewald_setup(const ewald_params_t* params, ewald_plan** plan) {
   // tile overrides for experiments and tests: MPEWALD_BWD = 1|2 (VALU Horner,
   // atoms per lane), 3|4 (matrix cores, 16|32 atoms per wave), 5 (matrix cores
   // with separate epilogue waves) or 6 (matrix cores, y phases in LDS);
-  // MPEWALD_SERIAL = 1 runs the adjoint chain on the caller's stream;
-  // MPEWALD_BATCH_SERIAL = 0|1 overrides the batches' choice of one stream;
+  // MPEWALD_SERIAL = 0|1 overrides the choice of one stream for single frames
+  // (1 for batches too), MPEWALD_BATCH_SERIAL = 0|1 for batches;
   // MPEWALD_BATCH_TARGET = a batch's forward block count target; MPEWALD_FWD =
   // 0|1 (VALU | matrix cores); MPEWALD_FWD_CT = 1|2|4 (matrix-core column
   // tiles per wave); MPEWALD_FWD_PF = 0|1 (VALU prefetch); MPEWALD_FWD_TARGET =
@@ -996,8 +1021,9 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
   if (ctx && !q.plain) {
     plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
     CtxView cv = ctx_view(plan->g, ctx, n_qm, n_mm);
-    st = seq_fwd_bwd(q, plan->serial ? s : plan->aux, plan->serial ? s : plan->aux2, qm_xyz, Q, mu, theta, mm_xyz, mm_q, cv.smm, plan->g.KF, energy, phi, efield,
-                     efgrad, cv.site, cv.gq, cv.gQ, cv.gmu, cv.gth, cv.gm, cv.gmq);
+    const bool one = plan->serial < 0 ? frame_one_stream(plan, q) : plan->serial != 0;
+    st = seq_fwd_bwd(q, one ? s : plan->aux, one ? s : plan->aux2, qm_xyz, Q, mu, theta, mm_xyz, mm_q, cv.smm,
+                     plan->g.KF, energy, phi, efield, efgrad, cv.site, cv.gq, cv.gQ, cv.gmu, cv.gth, cv.gm, cv.gmq);
     plan->t = saved;
     return st;
   }
@@ -1176,7 +1202,7 @@ ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int 
   Work& w = plan->w;
   const Grid& g = plan->g;
   if (mode == EWALD_FWD_BWD) {
-    const bool one = plan->serial || batch_one_stream(plan, mesh);
+    const bool one = plan->serial > 0 || batch_one_stream(plan, mesh);
     return seq_fwd_bwd(q, one ? s : plan->gaux, one ? s : plan->gaux2, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w.smm,
                        g.KF, energy, phi, efield, efgrad, w.site, g_qm_xyz, g_Q, g_mu, g_theta, g_mm_xyz, g_mm_q);
   }
