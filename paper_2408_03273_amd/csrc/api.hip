@@ -199,14 +199,16 @@ size_t mesh_frame_doubles(const Mesh& m) {
 constexpr size_t kMeshAtomDoubles = 48 + 4 + 1 + 1;
 
 // Whether the gridded sums are the faster: with F frames and n MM atoms in all,
-// dense sums cost about 0.22 ps per (atom, k vector), gridded ones 2.2 ns per
-// atom, 22 ps per mesh point of each frame and some 70 us for the longer chain
-// of launches (from batches of 16 and single frames of 600 to 60 000 atoms at
-// kmax 8 to 32; e.g. 16 frames of 6000 atoms at kmax 24: 1551 us dense, 1007
-// gridded; at kmax 12: 467 and 524).
+// dense sums cost about 0.2 ps per (atom, k vector), gridded ones as much per
+// atom as 7000 k vectors, 28 ps per mesh point of each frame and some 60 us for
+// the longer chain of launches.  Crossing points, dense against gridded in us:
+// one frame of 35 000 atoms at kmax 12 211 and 240, at kmax 16 261 and 233, of
+// 10 000 at kmax 20 208 and 220, at kmax 24 259 and 220, of 100 000 at kmax 12 331
+// and 352; 32 frames of 2000 at kmax 16 601 and 652, of 6000 1185 and 860; at
+// kmax 10 dense up to 20 000 each (1408 and 1578).
 bool mesh_pays(const Mesh& m, int KF, double n_frames, double atoms) {
   const double points = (double)m.N[0] * m.N[1] * m.N[2];
-  return atoms * ((double)KF - 1e4) > 100.0 * points * n_frames + 3e8;
+  return atoms * (KF - 7e3) > 130.0 * points * n_frames + 3e8;
 }
 
 // Gridded or dense reciprocal sums for a call over these frames.  The mesh

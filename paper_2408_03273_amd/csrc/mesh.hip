@@ -22,13 +22,17 @@
 // derivative jumps by beta^2 / (2 I0(beta)) at the edge of the support) and
 // rising towards the band edge, where the Ewald weight
 // exp(-k^2 / 4 alpha^2) = exp(-A (n/m)^2), A = (pi m / (alpha L))^2, outweighs
-// it.  N is chosen so that the product stays below 1e-16 (mesh_damping gives the
-// smallest A for which it does); a call with less damping takes the dense sums.
+// it.  N is chosen so that the product stays below 1e-14 at the worst n
+// (mesh_damping gives the smallest A for which it does); a call with less
+// damping takes the dense sums.  Few wave numbers come near that one, and the
+// outputs' errors stay those of the dense sums, 4e-16 to 1e-14: they are the same
+// to a digit with 1e-16 (a fifth more points per axis), while 7e-13 at the worst n
+// raises the MM gradient's from 5e-16 to 2e-14 (35 000 charges at kmax 24).
 // Everything is FP64.
 //
 // Measured against the dense sums (both directions, kernels alone): 16 frames of
-// 100 000 charges at kmax 32 41 ms dense, 4.3 ms here; 64 frames of 5000 to
-// 30 000 at kmax 20 8.3 and 3.6 ms; one frame of 35 000 at kmax 24 440 and 190 us.
+// 100 000 charges at kmax 32 41 ms dense, 3.5 ms here; 64 frames of 5000 to
+// 30 000 at kmax 20 8.3 and 2.4 ms; one frame of 35 000 at kmax 24 440 and 150 us.
 //
 // Real basis.  The mesh is real, so every contraction runs over the real
 // functions cos(2 pi n x/L), n = 0..m, and sin(2 pi n x/L), n = 1..m of each
@@ -1077,9 +1081,9 @@ static constexpr double kMeshBeta = 42.5;
 static constexpr int kMeshWidth = 16;
 
 // Smallest damping A at the band edge of |n| <= m on N points for which the
-// aliasing, weighted with exp(-A (n/m)^2), stays below 1e-16 at every n.
+// aliasing, weighted with exp(-A (n/m)^2), stays below 1e-14 at every n.
 double mesh_damping(int N, int m) {
-  const double pw = kPiM * kMeshWidth, need = 36.8;  // -ln 1e-16
+  const double pw = kPiM * kMeshWidth, need = 32.2;  // -ln 1e-14
   auto S = [&](double v) { return sqrt(std::max(0.0, kMeshBeta * kMeshBeta - pw * pw * v * v)); };
   double A = 0.0;
   for (int n = 1; n <= m; n++) {

@@ -5,7 +5,7 @@ of unequal and of the smallest size, frames without atoms, boxes whose Ewald
 weights fall off too little for the plan's mesh (dense sums then), and fixed
 order in deterministic plans.
 
-Tolerance: the aliasing stays below 1e-16 of the sum; FP64 rounding over up to
+Tolerance: the aliasing stays below 1e-14 of the sum; FP64 rounding over up to
 1e5 terms as a random walk gives 3e2 x 1.1e-16 = 4e-14, and the gradients cancel
 about one digit: 1e-12 of each output's largest element."""
 import numpy as np

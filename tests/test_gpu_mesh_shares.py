@@ -24,7 +24,7 @@ def _frame(seed, nm, box, kmax, clump):
     return s
 
 
-@pytest.mark.parametrize("kmax,n_frames,shares", [((12, 12, 12), 1, 4), ((24, 24, 24), 1, 2), ((24, 24, 24), 2, 1)])
+@pytest.mark.parametrize("kmax,n_frames,shares", [((12, 12, 12), 1, 4), ((28, 28, 28), 1, 2), ((28, 28, 28), 2, 1)])
 @pytest.mark.parametrize("nm,clump", [(1, False), (31, True), (33, True), (2049, False)])
 def test_spread_shares(kmax, n_frames, shares, nm, clump, monkeypatch):
     monkeypatch.setenv("MPEWALD_MESH", "1")
