@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256 * KS, KS == 4 ? 4 : 6) void k_mesh_spread(Mesh 
   __shared__ double staged[KS][kSpreadChunk * kSpreadAtom + kSpreadTail];
   __shared__ int cells[KS][kSpreadChunk];
   __shared__ int sources[KS][256];
-  __shared__ int4 list[4 * KS][kSpreadChunk + 12];
+  __shared__ int2 list[4 * KS][kSpreadChunk + 12];
   __shared__ int row_off[kSpreadRows + 1], row_s0[kSpreadRows], row_l0[kSpreadRows], row_s1[kSpreadRows];
   const int f = blockIdx.y;
   const MeshFrame fr = mesh_frame(fa, f);
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(256 * KS, KS == 4 ? 4 : 6) void k_mesh_spread(Mesh 
     if (t + 1 < rounds) load(t + 1);
     {
       bool hit = false;
-      int4 ad = make_int4(0, 0, 0, 0);
+      int2 ad = make_int2(0, 0);  // byte addresses of its first point: x | y << 16, z
       if (lane < n) {
         const int e = pk[lane];
         // first mesh point of the atom relative to the wave's part
@@ -419,29 +419,31 @@ __global__ __launch_bounds__(256 * KS, KS == 4 ? 4 : 6) void k_mesh_spread(Mesh 
         hit = rx <= 15 && ry >= -15 && ry <= 3 && rz >= -15 && rz <= 7;
         // tap j of an axis sits at its first tap + j; the part's first point reads tap -r
         const int b = 8 * lane * kSpreadAtom;
-        ad = make_int4(b + 8 * (kSpreadX - rx), b + 8 * (kSpreadY - ry), b + 8 * (kSpreadZ - rz), 0);
+        ad = make_int2((b + 8 * (kSpreadX - rx)) | (b + 8 * (kSpreadY - ry)) << 16, b + 8 * (kSpreadZ - rz));
       }
       const unsigned long long mask = __ballot(hit);
       const int cnt = (int)__popcll(mask);
-      int4* lw = list[4 * share + wave];
+      int2* lw = list[4 * share + wave];
       if (hit) lw[__popcll(mask & ((1ull << lane) - 1ull))] = ad;
       // padding to whole steps and for the reads ahead: the zeros at the end
-      if (lane < 12) lw[cnt + lane] = make_int4(8 * kSpreadChunk * kSpreadAtom, 8 * kSpreadChunk * kSpreadAtom, 8 * kSpreadChunk * kSpreadAtom, 0);
+      constexpr int kNone = 8 * kSpreadChunk * kSpreadAtom;
+      static_assert(kNone + 8 * kSpreadTail <= 32768, "16-bit addresses");
+      if (lane < 12) lw[cnt + lane] = make_int2(kNone | kNone << 16, kNone);
       lds_wave_sync();
       // four atoms per step: the operands of the next step are read and the list
       // entries of the one after while this step is contracted
       const char* __restrict__ tb = (const char*)tp;
       auto at = [&](int byte, int u) { return ((const double*)(tb + byte))[u]; };
-      int4 e = lw[lk];
-      double x = at(e.x + xq, 0), p0, p1;
+      int2 e = lw[lk];
+      double x = at((e.x & 0xffff) + xq, 0), p0, p1;
       {
-        const double y = at(e.y + yq, 0);
-        p0 = y * at(e.z + zq, 0);
-        p1 = y * at(e.z + zq, 4);
+        const double y = at((e.x >> 16) + yq, 0);
+        p0 = y * at(e.y + zq, 0);
+        p1 = y * at(e.y + zq, 4);
       }
       e = lw[4 + lk];
       for (int s = 0; s < cnt; s += 4) {
-        const double nx = at(e.x + xq, 0), ny = at(e.y + yq, 0), nz0 = at(e.z + zq, 0), nz1 = at(e.z + zq, 4);
+        const double nx = at((e.x & 0xffff) + xq, 0), ny = at((e.x >> 16) + yq, 0), nz0 = at(e.y + zq, 0), nz1 = at(e.y + zq, 4);
         e = lw[s + 8 + lk];
         __builtin_amdgcn_sched_barrier(0);
         acc[0] = mfma(x, p0, acc[0]);
