@@ -377,7 +377,8 @@ FrameDev make_frame(const double box[3], int nq, int nm, int qoff, int moff, int
 // Cells of edge >= rcut per axis (capped); the cell list is used only when
 // every frame has at least 3 cells per axis, else real space runs over all
 // pairs.  Returns whether the cell list is used and fills nc/cell_base.
-bool assign_cells(const ewald_plan* pl, FrameDev* frames, int n) {
+// both: forward and adjoint in one sequence.
+bool assign_cells(const ewald_plan* pl, FrameDev* frames, int n, bool both) {
   // (the cell fill orders atoms with atomics: deterministic plans sum over all pairs)
   bool ok = (pl->p.flags & EWALD_CELL_LIST) != 0 && !(pl->p.flags & EWALD_DETERMINISTIC);
   // Building the list costs a few kernel launches; over all pairs, real space
@@ -386,11 +387,21 @@ bool assign_cells(const ewald_plan* pl, FrameDev* frames, int n) {
   // product is large (measured: 38 million tests over the 64 c4 frames run
   // faster over all pairs, 128 million over the 16 c5 replicas over cells),
   // unless MPEWALD_CELLS forces the choice.
-  long pairs = 0;
-  for (int f = 0; f < n; f++) pairs += (long)frames[f].nq * frames[f].nm;
+  // Forward and adjoint by tiles of MM atoms cost 1.9 ps per test, the two passes
+  // over cells 0.36 us per site and 60 ns per 1000 atoms for the lists (16
+  // frames of 80 sites and 100 000 atoms: 243 us against 464 and 95): cells
+  // from about 190 000 atoms per frame on.
+  long pairs = 0, sites = 0;
+  int max_nm = 0;
+  for (int f = 0; f < n; f++) {
+    pairs += (long)frames[f].nq * frames[f].nm;
+    sites += frames[f].nq;
+    max_nm = std::max(max_nm, frames[f].nm);
+  }
+  const bool tiles = both && real_by_tiles(n, max_nm);
   int force = -1;
   if (const char* e = getenv("MPEWALD_CELLS")) force = atoi(e) ? 1 : 0;
-  if (force == 0 || (force < 0 && pairs < 64000000L)) ok = false;
+  if (force == 0 || (force < 0 && (pairs < 64000000L || (tiles && pairs < 190000L * sites)))) ok = false;
   for (int f = 0; f < n && ok; f++)
     for (int a = 0; a < 3; a++)
       if ((int)std::floor(frames[f].box[a] / pl->p.rcut) < 3) ok = false;
@@ -1016,7 +1027,7 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
   q.fa.frames = nullptr;
   q.fa.f0 = make_frame(plan->p.box, n_qm, n_mm, 0, 0, 0, plan->p.rcut);
   q.fa.n_frames = 1;
-  q.cells = assign_cells(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.cells = assign_cells(plan, &q.fa.f0, 1, ctx && !q.plain) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
   q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
   if (ctx) plan->stale_ctx.erase(ctx);
@@ -1097,7 +1108,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   q.fa.n_frames = 1;
   q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
   plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
-  q.cells = assign_cells(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.cells = assign_cells(plan, &q.fa.f0, 1, false) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
   CtxView cv = ctx_view(plan->g, (void*)ctx, n_qm, n_mm);
   Work& w = plan->w;
@@ -1289,7 +1300,7 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
   use.fwd_units = n_frames > 1 ? slot : 0;
   const int mesh = use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
   use.kc = mesh ? 1 : choose_kc(plan, total_nm);
-  const int cells = assign_cells(plan, hf.data(), n_frames) ? 1 : 0;
+  const int cells = assign_cells(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD) ? 1 : 0;
   const int mm_groups = real_mm_groups(plan, hf.data(), n_frames);
   // graph key: frames, pointers, mode, stream, tiles
   std::vector<unsigned char> key;

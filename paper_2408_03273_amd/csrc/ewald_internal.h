@@ -287,6 +287,8 @@ hipError_t launch_force_mm(const Grid& g, const Tuning& t, const FrameArg& fa, i
 // null) also receives the MM-side adjoint terms: from each pair of the
 // QM-side kernel (mm_groups 0), or from the per-atom kernel over mm_groups
 // site groups (deterministic plans: one group)
+// forward and adjoint in one pass by tiles of MM atoms (minimum image only)
+bool real_by_tiles(int n_frames, int max_nm);
 hipError_t launch_real_qm(const Grid& g, const FrameArg& fa, int max_nq, int max_nm, int cap_qm, int cap_mm,
                           int backward, int fp32, Work& w, hipStream_t s, double* rpart = nullptr,
                           int mm_groups = 0);

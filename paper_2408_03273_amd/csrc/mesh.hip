@@ -722,24 +722,6 @@ DEV double lane_value(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// sum over the 16 lanes of a row, in every lane (rotations by 8, 4, 2, 1)
-template <int CTRL>
-DEV double row_rotate(double v) {
-  const unsigned long long b = __double_as_longlong(v);
-  const int lo = (int)(unsigned)(b & 0xffffffffu), hi = (int)(unsigned)(b >> 32);
-  const unsigned l2 = (unsigned)__builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true);
-  const unsigned h2 = (unsigned)__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
-  return __longlong_as_double((long long)(((unsigned long long)h2 << 32) | l2));
-}
-
-DEV double row_sum(double v) {
-  v += row_rotate<0x128>(v);
-  v += row_rotate<0x124>(v);
-  v += row_rotate<0x122>(v);
-  v += row_rotate<0x121>(v);
-  return v;
-}
-
 // A step's atoms among the sorted ones: lane r < 8 holds the first atom (s0)
 // and the running count (exc) of bin row r (2 in y, 4 in z).
 struct GatherStep {
