@@ -1151,9 +1151,16 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   } else {
     STEP(launch_force_mm(g, plan->t, q.fa, n_mm, plan->cap_mm, w, s));
   }
+  // Each pair once, both sides from the QM-side kernel (the MM side added to rpart),
+  // where there are no images and no fixed order is asked for: 30 sites and 19 200 atoms
+  // with field gradients 422 -> 407 us, 200 sites 767 -> 592, 40 and 200 000 1035 -> 964.
+  const bool pairwise = !w.det_real && q.mm_groups == 0;
   if (q.cells) {
     STEP(launch_zero(w.rpart, (size_t)plan->cap_mm * 4, s));
     STEP(launch_real_cells(g, q.fa, n_qm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s));
+  } else if (pairwise) {
+    STEP(launch_zero(w.rpart, (size_t)n_mm * 4, s));
+    STEP(launch_real_qm(g, q.fa, n_qm, n_mm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s, w.rpart, 0));
   } else {
     // several site groups add into rpart from zero; one group writes it
     if (q.mm_groups > 1) STEP(launch_zero(w.rpart, (size_t)plan->cap_mm * 4, s));
@@ -1161,7 +1168,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   }
   STEP(launch_reduce_mm(g, plan->t, q.fa, n_mm, plan->cap_mm, g_mm_xyz, g_mm_q, w, s));
   STEP(launch_project_qm(g, q.fa, n_qm, cv.smm, g.KF, Q, mu, theta, 1, q.qmqm, w, s));
-  if (!q.cells) STEP(launch_real_qm(g, q.fa, n_qm, n_mm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s));
+  if (!q.cells && !pairwise) STEP(launch_real_qm(g, q.fa, n_qm, n_mm, plan->cap_qm, plan->cap_mm, 1, q.fp32, w, s));
   if (q.qmqm && n_qm > 0) STEP(launch_qmqm(g, q.fa, n_qm, plan->cap_qm, Q, mu, theta, w, s));
   STEP(launch_finalize_bwd(q.fa, n_qm, cv.site, gE, q.qmqm, g_qm_xyz, g_Q, g_mu, g_theta, w, s));
 #undef STEP
