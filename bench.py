@@ -40,7 +40,7 @@ def n_half_space(m):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "mesh.hip", "ewald_internal.h"):
+    for f in ("kernels.hip", "mesh.hip", "lanes.h", "ewald_internal.h"):
         with open(os.path.join(ROOT, "paper_2408_03273_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -283,14 +283,13 @@ ewald_status_t alloc_mesh(ewald_plan* pl) {
   const size_t q = (size_t)m.N[0] * m.N[1] * m.N[2], h = (size_t)m.N[0] * m.N[1] * m.C[2],
                c = (size_t)m.N[0] * m.C[1] * m.C[2], t = (size_t)m.C[0] * m.C[1] * m.C[2];
   std::vector<double> poly, fwd[3], bwd[3];
-  ewald_status_t st = EWALD_OK;
+  mesh_tables(m, poly, fwd, bwd);
+  // one allocation, carved in steps of 256 bytes: some twenty of their own took 1 ms of set-up
+  std::vector<std::pair<void**, size_t>> parts;
+  size_t bytes = 0;
   auto take = [&](auto** p, size_t n) {
-    if (st == EWALD_OK) st = alloc(pl, p, n);
-  };
-  auto upload = [&](double** p, const std::vector<double>& v) {
-    take(p, v.size());
-    if (st == EWALD_OK && hipMemcpy(*p, v.data(), v.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
-      st = fail(EWALD_ERR_HIP, "hipMemcpy failed");
+    parts.emplace_back((void**)p, bytes);
+    bytes += (n * sizeof(**p) + 255) / 256 * 256;
   };
   take(&w.mesh_cnt, cf * m.nbt);
   take(&w.mesh_start, cf * (m.nbt + 1));
@@ -307,13 +306,25 @@ ewald_status_t alloc_mesh(ewald_plan* pl) {
   take(&w.mesh_bh, cf * h);
   take(&w.mesh_v, cf * q);
   if (pl->p.flags & EWALD_DETERMINISTIC) take(&w.mesh_perm, cm);
+  // the tables last, side by side
+  const size_t tables = bytes;
+  std::vector<double> host;
+  auto table = [&](double** p, const std::vector<double>& v) {
+    take(p, v.size());
+    host.insert(host.end(), v.begin(), v.end());
+    host.resize((bytes - tables) / sizeof(double), 0.0);
+  };
+  table(&w.mesh_poly, poly);
+  for (int a = 0; a < 3; a++) {
+    table(&w.mesh_tab[a], fwd[a]);
+    table(&w.mesh_btab[a], bwd[a]);
+  }
+  char* base = nullptr;
+  ewald_status_t st = alloc(pl, &base, bytes);
   if (st == EWALD_OK) {
-    mesh_tables(m, poly, fwd, bwd);
-    upload(&w.mesh_poly, poly);
-    for (int a = 0; a < 3; a++) {
-      upload(&w.mesh_tab[a], fwd[a]);
-      upload(&w.mesh_btab[a], bwd[a]);
-    }
+    for (const auto& part : parts) *part.first = base + part.second;
+    if (hipMemcpy(base + tables, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+      st = fail(EWALD_ERR_HIP, "hipMemcpy failed");
   }
   // the bin counts start from zero (and every call leaves them so); the
   // padding of the weights on the real basis is never written
