@@ -283,8 +283,12 @@ ewald_status_t ewald_octupole_error_noalloc(const double box[3], int n_qm, const
  * and, with EWALD_FWD_BWD, of ewald_backward (paper: SI, Multipolar Ewald;
  * Results and Discussion, Timings, where the cost is the wall time per MD
  * step).  frames: host array of n_frames descriptors.
- * Packed inputs hold each frame's rows at its offsets.  mode: EWALD_FWD or
- * EWALD_FWD_BWD.  Outputs: energy (n_frames), phi/efield/efgrad per QM row;
+ * Packed inputs hold each frame's rows at its offsets.  No two frames may have
+ * QM rows in common.  Frames of the same box may share MM rows (several QM
+ * regions over one solvent; such a batch takes the dense reciprocal sums and all
+ * pairs): all outputs but g_mm_xyz and g_mm_q of the shared rows, which have one
+ * place for several frames' gradients, are those of the frames alone.
+ * mode: EWALD_FWD or EWALD_FWD_BWD.  Outputs: energy (n_frames), phi/efield/efgrad per QM row;
  * with EWALD_FWD_BWD also dE/dx for every input (gE = 1): g_qm_xyz, g_Q,
  * g_mu, g_theta per QM row, g_mm_xyz and g_mm_q (may be null) per MM row.
  * The launch sequence of one frame shape is captured once in a HIP graph and

@@ -388,10 +388,11 @@ FrameDev make_frame(const double box[3], int nq, int nm, int qoff, int moff, int
 // Cells of edge >= rcut per axis (capped); the cell list is used only when
 // every frame has at least 3 cells per axis, else real space runs over all
 // pairs.  Returns whether the cell list is used and fills nc/cell_base.
-// both: forward and adjoint in one sequence.
-bool assign_cells(const ewald_plan* pl, FrameDev* frames, int n, bool both) {
+// both: forward and adjoint in one sequence; shared: frames share MM rows (the
+// list has one place per row).
+bool assign_cells(const ewald_plan* pl, FrameDev* frames, int n, bool both, bool shared = false) {
   // (the cell fill orders atoms with atomics: deterministic plans sum over all pairs)
-  bool ok = (pl->p.flags & EWALD_CELL_LIST) != 0 && !(pl->p.flags & EWALD_DETERMINISTIC);
+  bool ok = (pl->p.flags & EWALD_CELL_LIST) != 0 && !(pl->p.flags & EWALD_DETERMINISTIC) && !shared;
   // Building the list costs a few kernel launches; over all pairs, real space
   // costs one distance test per (QM site, MM atom), and its waves evaluate
   // only the pairs within the cutoff (compacted).  Use cells only when that
@@ -1249,6 +1250,21 @@ ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int 
   return seq_forward_tail(q, Q, mu, theta, w.smm, g.KF, energy, phi, efield, efgrad, w.site);
 }
 
+// Whether two frames have MM rows in common (several QM regions over one solvent).
+bool share_mm_rows(const ewald_frame_t* frames, int n) {
+  std::vector<std::pair<int, int>> rows;  // first row, rows
+  bool sorted = true;
+  for (int f = 0; f < n; f++) {
+    if (frames[f].n_mm == 0) continue;
+    sorted = sorted && (rows.empty() || rows.back().first <= frames[f].mm_offset);
+    rows.emplace_back(frames[f].mm_offset, frames[f].n_mm);
+  }
+  if (!sorted) std::sort(rows.begin(), rows.end());
+  for (size_t i = 1; i < rows.size(); i++)
+    if ((long)rows[i - 1].first + rows[i - 1].second > rows[i].first) return true;
+  return false;
+}
+
 template <typename T>
 void key_push(std::vector<unsigned char>& k, const T& v) {
   const unsigned char* p = (const unsigned char*)&v;
@@ -1316,9 +1332,13 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
     slot += (fr.n_mm + use.a_chunk - 1) / use.a_chunk;
   }
   use.fwd_units = n_frames > 1 ? slot : 0;
-  const int mesh = use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
+  // The mesh sorts each frame's atoms and the cell list orders them, both with one
+  // place per MM row; the tables of the dense sums hold the same values in a row for all
+  // frames of one box that share it.
+  const bool shared = share_mm_rows(frames, n_frames);
+  const int mesh = !shared && use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
   use.kc = mesh ? 1 : choose_kc(plan, total_nm);
-  const int cells = assign_cells(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD) ? 1 : 0;
+  const int cells = assign_cells(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD, shared) ? 1 : 0;
   const int mm_groups = real_mm_groups(plan, hf.data(), n_frames);
   // graph key: frames, pointers, mode, stream, tiles
   std::vector<unsigned char> key;
