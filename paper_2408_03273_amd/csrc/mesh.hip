@@ -487,15 +487,18 @@ __global__ __launch_bounds__(256 * KS, KS == 4 ? 4 : 6) void k_mesh_spread(Mesh 
 // out[b][M][n] = sum_k tab[M][k] in[b][k][n] on the matrix cores: tab in A
 // fragment order [M tile][K step][64 lanes]; one 16 x 32 output part per wave
 // (the table fragment serves two column tiles), K in chunks of four steps
-// whose loads are issued before the previous chunk is contracted.
+// whose loads are issued before the previous chunk is contracted.  The parts of
+// all b lie in the grid's x: b runs over frames times x planes along y, more than
+// the 65 536 that y takes from 1366 frames on a mesh of 48 planes.
 __global__ __launch_bounds__(256) void k_mesh_left(const double* __restrict__ tab, const double* __restrict__ in,
-                                                   double* __restrict__ out, int m_tiles, int K, int cols) {
+                                                   double* __restrict__ out, int m_tiles, int K, int cols, int batch) {
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-  const int c_pairs = (cols + 31) / 32;
-  const int unit = blockIdx.x * 4 + uni((int)(threadIdx.x >> 6));
-  if (unit >= m_tiles * c_pairs) return;
+  const int c_pairs = (cols + 31) / 32, per = m_tiles * c_pairs;
+  const int part = blockIdx.x * 4 + uni((int)(threadIdx.x >> 6));
+  const int b = part / per, unit = part - b * per;
+  if (b >= batch) return;
   const int cp = unit / m_tiles, mt = unit - cp * m_tiles;
-  const double* __restrict__ src = in + (size_t)blockIdx.y * K * cols;
+  const double* __restrict__ src = in + (size_t)b * K * cols;
   const int c0 = 32 * cp + li, c1 = min(c0 + 16, cols - 16 + li);
   const double* __restrict__ ta = tab + (size_t)mt * (K / 4) * 64 + lane;
   const double* __restrict__ p0 = src + (size_t)lk * cols + c0;
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(256) void k_mesh_left(const double* __restrict__ ta
       y[u] = yn[u];
     }
   }
-  double* __restrict__ o = out + ((size_t)blockIdx.y * m_tiles * 16 + mt * 16 + lk) * cols;
+  double* __restrict__ o = out + ((size_t)b * m_tiles * 16 + mt * 16 + lk) * cols;
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     o[(size_t)4 * r * cols + c0] = acc0[r];
@@ -971,8 +974,9 @@ __global__ __launch_bounds__(64 * kGatherWaves) void k_mesh_gather(Mesh m, Frame
 // ------------------------------------------------------------------ launchers
 static hipError_t left(const double* tab, const double* in, double* out, int m, int K, int cols, int batch,
                        hipStream_t s) {
-  const int units = (m / 16) * ((cols + 31) / 32);
-  hipLaunchKernelGGL(k_mesh_left, dim3((units + 3) / 4, batch), dim3(256), 0, s, tab, in, out, m / 16, K, cols);
+  // (below 2^24: each writes at least 256 numbers of the mesh workspace, which is held to kMeshMaxBytes)
+  const int parts = (m / 16) * ((cols + 31) / 32) * batch;
+  hipLaunchKernelGGL(k_mesh_left, dim3((parts + 3) / 4), dim3(256), 0, s, tab, in, out, m / 16, K, cols, batch);
   return hipGetLastError();
 }
 
