@@ -48,7 +48,7 @@ def kernel_source_hash() -> str:
 
 def recip_flops(desc: str, kmax, nm: float, frames: int = 1):
     """FP64 flops of the reciprocal sums over the MM charges, per kernel group:
-    algorithmic and executed.  Gridded sums (the plan names its mesh): each
+    algorithmic and executed.  Gridded sums (the plan's last call took its mesh): each
     charge meets 16^3 mesh points, one multiply-add per point when spread, two
     (value and derivative) when read; the mesh is contracted with the real basis
     of 2 m + 1 functions per axis, z, y, x, and back.  Dense sums, per (k in the
@@ -57,7 +57,7 @@ def recip_flops(desc: str, kmax, nm: float, frames: int = 1):
     p kz0 z per (column, |nz|) covers both k = (kx, ky, +-p kz0)), adjoint 6 (the
     forces); executed by the matrix-core kernels 4 and 8 (the adjoint also forms
     the potential, dE/dq, and the nz-weighted sums)."""
-    m = re.search(r"mesh=(\d+)x(\d+)x(\d+)", desc)
+    m = re.search(r"mesh=(\d+)x(\d+)x(\d+) sums=mesh", desc)
     if m:
         n0, n1, n2 = (int(v) for v in m.groups())
         c0, c1, c2 = (2 * k + 1 for k in kmax)
@@ -377,7 +377,6 @@ def _per_config(dev, no_autotune, steps=5):
         plan = Plan(EwaldConfig(box=tuple(s.box), alpha=s.alpha, rcut=s.rcut, kmax=s.kmax, max_qm=s.nq, max_mm=s.nm))
         if not no_autotune:
             plan.autotune(s.nm)
-        fl = sum(recip_flops(plan.describe(), s.kmax, float(s.nm))[0].values())
         x = [torch.tensor(a, dtype=torch.float64, device=dev, requires_grad=True)
              for a in (s.qm_pos, s.Q, s.mu, s.theta, s.mm_pos, s.q)]
 
@@ -387,6 +386,7 @@ def _per_config(dev, no_autotune, steps=5):
             ewald(plan, *x)[0].backward()
 
         ms = timed(step, 4 * steps)
+        fl = sum(recip_flops(plan.describe(), s.kmax, float(s.nm))[0].values())
         # the same frame as a one-frame batch: the launch sequence replays as one HIP graph
         xd = [t.detach() for t in x]
         desc = [dict(box=s.box, n_qm=s.nq, n_mm=s.nm, qm_offset=0, mm_offset=0)]

@@ -317,7 +317,10 @@ ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char* cache_path
 ewald_status_t ewald_profile_report(ewald_plan* plan, char* buf, size_t len);
 
 /* Tile configuration in use (for reports): forward nz chunk, backward
- * columns per block, etc., as a short text. */
+ * columns per block, etc., as a short text.  Where the plan holds a mesh for
+ * gridded reciprocal sums, "mesh=AxBxC", and after the first call that sums over MM
+ * charges "sums=mesh" or "sums=dense", what the last such call took.  The text is valid
+ * until the next call of this function on the plan. */
 const char* ewald_plan_describe(const ewald_plan* plan);
 
 /* Message of the calling thread's last error ("" if none); every entry point

@@ -59,8 +59,10 @@ struct ewald_plan {
   Mesh mesh;
   bool mesh_ok = false;
   int mesh_mode = -1;
+  int last_mesh = -1;  // the last call's choice: 1 the mesh, 0 the dense sums, -1 none yet
   std::vector<void*> allocs;
   std::string describe;
+  mutable std::string described;  // describe and the last call's choice
   // batched graph state
   hipStream_t gstream = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -1012,7 +1014,13 @@ size_t ewald_ctx_bytes(const ewald_plan* plan, int n_qm, int n_mm) {
   return ctx_bytes(plan->g, n_qm, n_mm);
 }
 
-const char* ewald_plan_describe(const ewald_plan* plan) { return plan ? plan->describe.c_str() : ""; }
+const char* ewald_plan_describe(const ewald_plan* plan) {
+  if (!plan) return "";
+  plan->described = plan->describe;
+  if (plan->last_mesh >= 0 && plan->mesh_ok && plan->mesh_mode != 0)
+    plan->described += plan->last_mesh ? " sums=mesh" : " sums=dense";
+  return plan->described.c_str();
+}
 
 ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, const double* Q, const double* mu,
                              const double* theta, int n_mm, const double* mm_xyz, const double* mm_q,
@@ -1041,7 +1049,7 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
   q.fa.n_frames = 1;
   q.cells = assign_cells(plan, &q.fa.f0, 1, ctx && !q.plain) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
-  q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
   if (ctx) plan->stale_ctx.erase(ctx);
   if (ctx && !q.plain) {
     plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
@@ -1118,7 +1126,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   q.fa.frames = nullptr;
   q.fa.f0 = make_frame(plan->p.box, n_qm, n_mm, 0, 0, 0, plan->p.rcut);
   q.fa.n_frames = 1;
-  q.mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
   plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
   q.cells = assign_cells(plan, &q.fa.f0, 1, false) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
@@ -1336,7 +1344,7 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
   // place per MM row; the tables of the dense sums hold the same values in a row for all
   // frames of one box that share it.
   const bool shared = share_mm_rows(frames, n_frames);
-  const int mesh = !shared && use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
+  const int mesh = plan->last_mesh = !shared && use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
   use.kc = mesh ? 1 : choose_kc(plan, total_nm);
   const int cells = assign_cells(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD, shared) ? 1 : 0;
   const int mm_groups = real_mm_groups(plan, hf.data(), n_frames);
@@ -1776,7 +1784,7 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
   hipEvent_t e0 = nullptr, e1 = nullptr;
   ewald_status_t st = EWALD_OK;
   const Tuning saved = plan->t;
-  const int saved_mesh = plan->mesh_mode;
+  const int saved_mesh = plan->mesh_mode, saved_last = plan->last_mesh;
   plan->mesh_mode = 0;  // the tiles are those of the dense sums
   double best_f = 1e30, best_b = 1e30;
   Tuning best = saved;
@@ -1990,6 +1998,7 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
 done:
 #undef TCHK
   plan->mesh_mode = saved_mesh;
+  plan->last_mesh = saved_last;
   plan->t = st == EWALD_OK ? best : saved;
   plan->t.a_chunk = 0;
   if (s) (void)hipStreamSynchronize(s);
