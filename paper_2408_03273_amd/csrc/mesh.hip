@@ -944,14 +944,12 @@ __global__ __launch_bounds__(64 * kGatherWaves) void k_mesh_gather(Mesh m, Frame
         // every wave counts in once per step, whether it has atoms or not, and
         // waits only for counts of the step before: all of them come
         if (k > 0)
-          while (__hip_atomic_load(&counted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < k * kGatherWaves)
+          while (__hip_atomic_load(&counted, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < k * kGatherWaves)
             __builtin_amdgcn_s_sleep(1);
-        asm volatile("" ::: "memory");
         if (k + 1 < len) {
           put_step(k + 1);
-          // (LDS operations of a wave take effect in order: the count follows the points)
-          asm volatile("" ::: "memory");
-          if (lane == 0) __hip_atomic_fetch_add(&counted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          // the count releases the points written, and the reads of the steps before, of all lanes of the wave
+          if (lane == 0) __hip_atomic_fetch_add(&counted, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
           if (k + 2 < len) load_step(k + 2);
         }
       };
