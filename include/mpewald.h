@@ -74,7 +74,9 @@ enum {
                               folded weights rounded to FP32, FP32 accumulation inside
                               a block, FP64 sums across blocks and everything after;
                               needs kmax[2] <= 32 and kmax[1] <= 61.  The error against
-                              FP64 is of the order of 1e-6 relative (mixed precision) */
+                              FP64 is of the order of 1e-6 relative (mixed precision).
+                              Always dense sums: where EWALD_FP64 takes its mesh (see
+                              ewald_setup), that is both more accurate and faster */
 };
 
 /* flags */
@@ -86,7 +88,8 @@ enum {
   EWALD_PROFILE = 8,       /* time every kernel launch with events on its stream
                               (single-frame calls only; read with ewald_profile_report) */
   EWALD_PROFILE_HOT = 16,  /* as EWALD_PROFILE, but only the two reciprocal-space
-                              hot loops (sfac_mm, force_mm): two events per launch */
+                              hot loops (sfac_mm, force_mm; on the mesh the launch groups
+                              mesh_sfac, mesh_force): two events each */
   EWALD_NO_BACKGROUND = 32, /* leave out the uniform neutralising background of charged
                               subsystems, -(pi/(2 a^2 V)) Qtot^2 and -(pi/(a^2 V)) Qtot qtot,
                               which is included by default (the paper is silent on it;
@@ -126,7 +129,18 @@ typedef struct {
  * the given capacities.  The plan keeps a copy of *params: the Ewald
  * splitting parameter, real-space cutoff and k-space range of the multipolar
  * Ewald sums (paper: SI, Multipolar Ewald; Computational Details, Common
- * Setup, for the choice of the cutoff). */
+ * Setup, for the choice of the cutoff).
+ * A plan whose max_mm allows calls large enough for gridded reciprocal sums (some
+ * 30 000 charges at kmax 16, 7000 at kmax 24; FP64 sums, not EWALD_PLAIN) also holds
+ * a mesh workspace beside that of the dense sums: 432 bytes per MM charge and
+ * about 50 bytes per mesh point and frame (35 000 charges on 80^3 39 MB, 16 frames of
+ * 100 000 on 96^3 1.4 GB), at most 32 GiB.  Where it would be larger, or its
+ * allocation fails, the plan keeps to the dense sums; with the environment variable
+ * MPEWALD_MESH=0 at setup it is left out.
+ * The mesh is sized for this box with a margin: a call takes the dense sums, with the
+ * same results in 3 to 10 times the time, if its box (in a batch, any frame's; after
+ * ewald_set_box, the new one) has an edge longer than this one by more than about a
+ * fifth.  ewald_plan_describe says what the last call took. */
 ewald_status_t ewald_setup(const ewald_params_t* params, ewald_plan** plan);
 
 /* Release the workspace of a plan made by ewald_setup; null is accepted. */
@@ -139,7 +153,10 @@ ewald_status_t ewald_set_box(ewald_plan* plan, const double box[3]);
 /* Bytes of the caller-allocated context that ewald_forward fills and
  * ewald_backward reads (saved reciprocal structure factor of the MM charges
  * and the MM potential data at the QM sites: the MM field that the SCF
- * iterations and the gradient reuse, paper: Electronic Mean-Field Theory). */
+ * iterations and the gradient reuse, paper: Electronic Mean-Field Theory).  Its
+ * layout is the library's own.  A structure factor from the mesh is accurate under
+ * its Ewald weight exp(-k^2 / 4 alpha^2), as every use here takes it: without the weight,
+ * elements near the largest |k| are off by up to 1e-5 of the largest element. */
 size_t ewald_ctx_bytes(const ewald_plan* plan, int n_qm, int n_mm);
 
 /* Forward pass (paper: periodic multipole energy; SI multipolar Ewald).
@@ -300,7 +317,8 @@ ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewald_frame_t* 
                            double* g_qm_xyz, double* g_Q, double* g_mu, double* g_theta, double* g_mm_xyz,
                            double* g_mm_q, void* stream);
 
-/* Time the candidate tilings of the two reciprocal-space kernels for a
+/* Time the candidate tilings of the two dense reciprocal-space kernels (calls that
+ * take the mesh do not use them) for a
  * system of n_mm MM charges (synthetic, with the plan's QM capacity up to 64
  * sites) on the plan's device: each kernel alone, then the finalists within
  * 3% of the best as whole forward+adjoint steps in interleaved rounds; keep

@@ -213,21 +213,42 @@ bool mesh_pays(const Mesh& m, int KF, double n_frames, double atoms) {
   return atoms * (KF - 7e3) > 130.0 * points * n_frames + 3e8;
 }
 
+// Which of the two sums over the MM charges a call forms.
+enum Sums { SUMS_FORWARD, SUMS_ADJOINT, SUMS_BOTH };
+
+// Whether spreading keeps up with the dense sums: a frame's few tiles on a small
+// mesh each go through a good part of its atoms, 3.1 us per round of chunks
+// (kernels of 48^3 to 96^3), where the dense forward takes 0.07 ps per (atom,
+// k vector) and both sums 0.2.  The lines lie where the measured times cross, us dense
+// against gridded.  Both: one frame of 60 000 atoms at kmax 14 on 48^3 280 and 467
+// (0.43 ps), on 64^3 279 and 250 (0.18), two of 30 000 on 48^3 437 and 367 (0.21).  Forward
+// alone: one of 35 000 at kmax 16 on 64^3 128 and 159 (0.12 ps), four of 30 000 at kmax 14
+// on 48^3 388 and 301 (0.11), one of 35 000 at kmax 18 on 64^3 159 and 161 (0.09).
+// The adjoint alone spreads nothing and was never slower than dense.
+bool mesh_spreads_in_time(const Mesh& m, int KF, int n_frames, double atoms, double max_nm, Sums sums) {
+  if (sums == SUMS_ADJOINT) return true;
+  const double us = 3.1 * mesh_spread_rounds(m, n_frames, max_nm);
+  return us < (sums == SUMS_FORWARD ? 0.115e-6 : 0.28e-6) * atoms * KF;
+}
+
 // Gridded or dense reciprocal sums for a call over these frames.  The mesh
 // needs the Ewald weights to fall off enough at the band edge in every frame's
 // box.
-bool use_mesh(const ewald_plan* pl, const FrameDev* frames, int n_frames) {
+bool use_mesh(const ewald_plan* pl, const FrameDev* frames, int n_frames, Sums sums) {
   if (!pl->mesh_ok || pl->mesh_mode == 0) return false;
   double atoms = 0.0;
+  int max_nm = 0;
   for (int f = 0; f < n_frames; f++) {
     for (int a = 0; a < 3; a++) {
       const double x = M_PI * pl->mesh.m[a] / (pl->p.alpha * frames[f].box[a]);
       if (!(x * x >= pl->mesh.damping[a])) return false;
     }
     atoms += frames[f].nm;
+    max_nm = std::max(max_nm, frames[f].nm);
   }
   if (atoms == 0.0) return false;
-  return pl->mesh_mode == 1 || mesh_pays(pl->mesh, pl->g.KF, n_frames, atoms);
+  return pl->mesh_mode == 1 || (mesh_pays(pl->mesh, pl->g.KF, n_frames, atoms) &&
+                                mesh_spreads_in_time(pl->mesh, pl->g.KF, n_frames, atoms, max_nm, sums));
 }
 
 int fwd_kblocks(const ewald_plan* pl) { return fwd_col_groups(pl->g, pl->t); }
@@ -1049,7 +1070,7 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
   q.fa.n_frames = 1;
   q.cells = assign_cells(plan, &q.fa.f0, 1, ctx && !q.plain) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
-  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1, ctx ? SUMS_BOTH : SUMS_FORWARD) ? 1 : 0;
   if (ctx) plan->stale_ctx.erase(ctx);
   if (ctx && !q.plain) {
     plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
@@ -1126,7 +1147,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
   q.fa.frames = nullptr;
   q.fa.f0 = make_frame(plan->p.box, n_qm, n_mm, 0, 0, 0, plan->p.rcut);
   q.fa.n_frames = 1;
-  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1) ? 1 : 0;
+  q.mesh = plan->last_mesh = use_mesh(plan, &q.fa.f0, 1, SUMS_ADJOINT) ? 1 : 0;
   plan->t.kc = q.mesh ? 1 : choose_kc(plan, n_mm);
   q.cells = assign_cells(plan, &q.fa.f0, 1, false) ? 1 : 0;
   q.mm_groups = real_mm_groups(plan, &q.fa.f0, 1);
@@ -1344,7 +1365,8 @@ extern "C" ewald_status_t ewald_batch(ewald_plan* plan, int n_frames, const ewal
   // place per MM row; the tables of the dense sums hold the same values in a row for all
   // frames of one box that share it.
   const bool shared = share_mm_rows(frames, n_frames);
-  const int mesh = plan->last_mesh = !shared && use_mesh(plan, hf.data(), n_frames) ? 1 : 0;
+  const int mesh = plan->last_mesh =
+      !shared && use_mesh(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD ? SUMS_BOTH : SUMS_FORWARD) ? 1 : 0;
   use.kc = mesh ? 1 : choose_kc(plan, total_nm);
   const int cells = assign_cells(plan, hf.data(), n_frames, mode == EWALD_FWD_BWD, shared) ? 1 : 0;
   const int mm_groups = real_mm_groups(plan, hf.data(), n_frames);

@@ -270,6 +270,10 @@ hipError_t launch_sfac_mm(const Grid& g, const Tuning& t, const FrameArg& fa, in
 bool mesh_shape(const Grid& g, const double box[3], Mesh& m);
 void mesh_tables(const Mesh& m, std::vector<double>& poly, std::vector<double> (&fwd)[3],
                  std::vector<double> (&bwd)[3]);
+// groups of waves that share a tile's atoms when spreading, and the chunks that a
+// group of the fullest tile takes one after another (n evenly spread atoms per frame)
+int mesh_shares(const Mesh& m, int n_frames);
+double mesh_spread_rounds(const Mesh& m, int n_frames, double n);
 hipError_t launch_mesh_sort(const Mesh& m, const FrameArg& fa, int max_nm, int cap_mm, Work& w, hipStream_t s);
 hipError_t launch_mesh_sfac(const Mesh& m, const FrameArg& fa, Work& w, hipStream_t s);
 hipError_t launch_mesh_smm(const Mesh& m, const Grid& g, const FrameArg& fa, double2* smm, size_t smm_stride, Work& w,

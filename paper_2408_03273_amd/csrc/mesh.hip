@@ -31,8 +31,13 @@
 // Everything is FP64.
 //
 // Measured against the dense sums (both directions, kernels alone): 16 frames of
-// 100 000 charges at kmax 32 41 ms dense, 3.5 ms here; 64 frames of 5000 to
-// 30 000 at kmax 20 8.3 and 2.4 ms; one frame of 35 000 at kmax 24 440 and 150 us.
+// 100 000 charges at kmax 32 41 ms dense, 3.4 ms here (meshes of 96^3); 64 frames of 5000
+// to 30 000 at kmax 20 8.3 and 2.4 ms (64^3); one frame of 35 000 at kmax 24 440 and
+// 150 us (80^3).
+//
+// The charges are taken to be spread over the box.  Where many share a few
+// tiles the time is that of the fullest ones: 35 000 charges all within 20 A of one point
+// of a 70 A box take 1.5 times as long as dense sums.
 //
 // Real basis.  The mesh is real, so every contraction runs over the real
 // functions cos(2 pi n x/L), n = 0..m, and sin(2 pi n x/L), n = 1..m of each
@@ -271,14 +276,16 @@ __global__ __launch_bounds__(256) void k_mesh_sort(Mesh m, FrameArg fa, const do
 // its first point.  The products phi_y phi_z of a step are formed before it, so
 // that its two matrix instructions follow each other.  A 4 x 4 part has less work
 // outside the support (31 19 19 / 16^3 = 2.7 times the useful multiply-adds,
-// 3.3 here) but twice the x reads.  Matrix cores and LDS are each busy about
-// half the time; 27 KB of LDS and 80 registers let six blocks share a CU and cover
-// each other's staging: 16 frames of 100 000 charges on a 112^3 mesh 1.67 ms with
-// chunks of 64 and three blocks, 1.37 ms so (matrix instructions alone 0.59 ms); 64
-// frames of 5000 to 30 000 on 80^3 1.13 -> 0.90 ms.  Where the tiles are too few for
-// six blocks per CU, KS shares of the atoms per block (each with its own
-// staging, summed in LDS at the end): one frame of 35 000 on 96^3 60 us with one
-// share, 49 with two, 53 with four; one of 19 200 on 64^3 81, 58 and 47 us.
+// 3.3 here) but twice the x reads.  In batches matrix cores and LDS are each busy
+// about half the time; 27 KB of LDS and 80 registers let six blocks share a CU and
+// cover each other's staging: 16 frames of 100 000 charges on a 112^3 mesh 1.67 ms with
+// chunks of 64 and three blocks, 1.37 ms so (matrix instructions alone 0.59 ms), 1.30 on
+// the 96^3 that these plans take; 64 frames of 5000 to 30 000 on 80^3 1.13 -> 0.90 ms, on
+// 64^3 0.82.  Where the tiles are too few for six blocks per CU, KS shares of the atoms
+// per block (each with its own staging, summed in LDS at the end): one frame of 35 000
+// on 80^3 (250 tiles) 75 us with one share, 54 with two, 44 with four, on 96^3 (432) 60,
+// 49 and 53; one of 19 200 on 64^3 (128) 81, 58 and 47 us.  A single frame waits for its own
+// staging: matrix cores and LDS 30% busy at 80^3.
 // A staged atom: [15 zeros | x taps | 15 zeros | y taps | 7 zeros | z taps], each
 // run of zeros (and the next atom's first one) padding the taps on both sides;
 // an odd number of doubles for the LDS banks.
@@ -710,8 +717,9 @@ __global__ __launch_bounds__(256) void k_mesh_wk(Mesh m, int KF, const double2* 
 // Measured against tiles of 8 x 8 x 16 cells, each staged whole, dealt to the
 // waves in turn: 16 frames of 100 000 charges on a 112^3 mesh 1.45 -> 1.38 ms (the
 // LDS reads alone 0.85 ms), 64 frames of 5000 to 30 000 on 80^3 1.62 -> 1.09 ms,
-// one of 35 000 on 96^3 54 -> 50 us.  With 8 waves 1.64 ms and 1.23 ms, with 16
-// (registers short) 1.43 and 1.17 ms.
+// one of 35 000 on 96^3 54 -> 50 us.  On the 96^3, 64^3 and 80^3 that these plans take
+// 1.23 ms, 0.90 ms and 42 us; with 8 waves 1.50, 1.07 and 47, with 16 (registers short)
+// 1.22, 0.93 and 50.
 static constexpr int kGatherY = 8, kGatherZ = 16;                        // cells of a column
 static constexpr int kGatherWY = kGatherY + 15, kGatherWZ = kGatherZ + 15;  // points of a plane
 static constexpr int kGatherWindow = 4 + 15;                             // planes a step reads
@@ -1012,18 +1020,29 @@ hipError_t launch_mesh_sort(const Mesh& m, const FrameArg& fa, int max_nm, int c
   return hipGetLastError();
 }
 
+// shares of a tile's atoms: as many as the 24 waves of each CU hold at once
+// (times of each beside the kernel)
+int mesh_shares(const Mesh& m, int n_frames) {
+  const long tiles = (long)(m.N[0] / 16) * (m.N[1] / 8) * (m.N[2] / 16) * n_frames;
+  return tiles <= 256 ? 4 : tiles <= 768 ? 2 : 1;
+}
+
+// a tile meets the atoms of 32 x 24 x 32 cells
+double mesh_spread_rounds(const Mesh& m, int n_frames, double n) {
+  const double cells = (double)m.N[0] * m.N[1] * m.N[2];
+  return n * (32.0 * 24.0 * 32.0) / cells / (kSpreadChunk * mesh_shares(m, n_frames));
+}
+
 hipError_t launch_mesh_sfac(const Mesh& m, const FrameArg& fa, Work& w, hipStream_t s) {
   const int F = fa.n_frames;
   const int tx = m.N[0] / 16, ty = m.N[1] / 8, tz = m.N[2] / 16;
-  // shares of a tile's atoms: as many as the 24 waves of each CU hold at once
-  // (times of each beside the kernel)
-  const int tiles = tx * ty * tz * F;
+  const int shares = mesh_shares(m, F);
 #define SPREAD(KS)                                                                                               \
   hipLaunchKernelGGL(k_mesh_spread<KS>, dim3(tx * ty * tz, F), dim3(256 * KS), 0, s, m, fa, tx, ty, tz,          \
                      w.mesh_start, w.mesh_taps, w.mesh_cell, w.mesh_q)
-  if (tiles <= 256)
+  if (shares == 4)
     SPREAD(4);
-  else if (tiles <= 768)
+  else if (shares == 2)
     SPREAD(2);
   else
     SPREAD(1);

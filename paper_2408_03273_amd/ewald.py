@@ -269,6 +269,7 @@ class Plan:
 
     def batch(self, frames, qm_pos, Q, mu, theta, mm_pos, mm_q, with_grad=True, out=None):
         """frames: list of dicts with box, n_qm, n_mm, qm_offset, mm_offset over packed arrays.
+        Frames of one box may share MM rows (their g_mm_pos and g_mm_q are then not defined).
 
         Pass the dict returned by a previous call as `out` to reuse the output
         tensors; with unchanged frames, inputs and outputs the library replays
@@ -315,8 +316,8 @@ class EwaldFunction(torch.autograd.Function):
     """E, phi, efield, efgrad = EwaldFunction.apply(plan, qm_pos, Q, mu, theta, mm_pos, mm_q).
 
     The backward pass is the library's adjoint (once differentiable).  The
-    forward call already evaluates the gradients of E (its adjoint kernel runs
-    beside the forward kernel on a second stream) and keeps them with the MM
+    forward call already evaluates the gradients of E (in one sequence of
+    launches with the forward sums) and keeps them with the MM
     structure factor and the MM field data in the saved context; a backward
     with upstream gradients only on E scales them, one with upstream gradients
     on phi/efield/efgrad re-runs the adjoint.  Phases e^{i k.r} are recomputed,
