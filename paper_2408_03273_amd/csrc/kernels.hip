@@ -2297,10 +2297,10 @@ DEV SiteMoments<T> site_moments(const double* qe) {
 //             Hessian of phi at the site);
 //   BWD != 0: dL/dR_site with the effective moments M into acc[OB..OB+2], and
 //             with mm_side the MM atom's terms into mm[0..3]: the potential of
-//             M per unit charge, and -q g.
+//             M per unit charge, and -q_mm g.
 template <typename T, int BWD>
 DEV void pair_terms(T x, T y, T z, T r2, T q, T a, const SiteMoments<T>& M, double* acc, bool mm_side,
-                    double (&mm)[4]) {
+                    double (&mm)[4], double q_mm) {
   constexpr int OB = BWD == 2 ? 10 : 0;
   const Radial<T> R = radial<T>(r2, a);
   if (BWD != 1) {
@@ -2333,9 +2333,9 @@ DEV void pair_terms(T x, T y, T z, T r2, T q, T a, const SiteMoments<T>& M, doub
     acc[OB + 2] += (double)q * gz;
     if (mm_side) {
       mm[0] = (double)(M.Q * R.f1 - md * R.f3 + T(1.5) * dtd * R.f5 - T(0.5) * tr * R.f3);
-      mm[1] = -(double)q * gx;
-      mm[2] = -(double)q * gy;
-      mm[3] = -(double)q * gz;
+      mm[1] = -q_mm * gx;
+      mm[2] = -q_mm * gy;
+      mm[3] = -q_mm * gz;
     }
   }
 }
@@ -2428,7 +2428,10 @@ DEV void real_qm_item(const Grid& g, const FrameDev& fr, int j, int ci, int nchu
   auto evaluate = [&](int n) {
     if (lane >= n) return;
     double mm[4];
-    pair_terms<T, BWD>(ff.x[lane], ff.y[lane], ff.z[lane], ff.r2[lane], ff.q[lane], a, M, acc, rpart != nullptr, mm);
+    // the MM side of the adjoint alone takes the charge as it is, as k_real_mm does
+    const double q_mm = BWD == 1 && sizeof(T) < sizeof(double) && rpart ? mq_[ff.idx[lane]] : (double)ff.q[lane];
+    pair_terms<T, BWD>(ff.x[lane], ff.y[lane], ff.z[lane], ff.r2[lane], ff.q[lane], a, M, acc, rpart != nullptr, mm,
+                       q_mm);
     if (BWD != 0 && rpart) {
       double* o = rpart + (size_t)(fr.moff + ff.idx[lane]) * 4;
       for (int t = 0; t < 4; t++) atomicAdd(&o[t], mm[t]);
@@ -2582,7 +2585,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     auto evaluate = [&](int n) {
       if (lane >= n) return;
       double mm[4];
-      pair_terms<T, 2>(ff.x[lane], ff.y[lane], ff.z[lane], ff.r2[lane], ff.q[lane], a, M, acc, true, mm);
+      pair_terms<T, 2>(ff.x[lane], ff.y[lane], ff.z[lane], ff.r2[lane], ff.q[lane], a, M, acc, true, mm,
+                         (double)ff.q[lane]);
       const int k = ff.idx[lane];
       for (int t = 0; t < 4; t++) atomicAdd(&mmacc[t * 256 + k], mm[t]);
     };
@@ -2723,7 +2727,7 @@ __global__ __launch_bounds__(64 * kTileWaves, 4) void k_real_tile(Grid g, FrameA
       const int i = ff[lane];
       double x, y, z, mm[4];
       const double r2 = offset(i, x, y, z);
-      pair_terms<T, 2>((T)x, (T)y, (T)z, (T)r2, (T)pos[3][i], a, M, acc, true, mm);
+      pair_terms<T, 2>((T)x, (T)y, (T)z, (T)r2, (T)pos[3][i], a, M, acc, true, mm, (double)(T)pos[3][i]);
 #pragma unroll
       for (int t = 0; t < 4; t++)
         __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double*)&side[t][i], mm[t]);
