@@ -139,8 +139,18 @@ __global__ __launch_bounds__(64) void k_det_reduce(FrameArg fa, int mode, const 
     row = (size_t)f;
     base = (size_t)f * nb * stride;
   }
+  // eight partials in flight, added in order
+  const double* __restrict__ p = src + base + t;
   double sum = 0.0;
-  for (int b = 0; b < count; b++) sum += src[base + (size_t)b * step + t];
+  int b = 0;
+  for (; b + 8 <= count; b += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) v[u] = p[(size_t)(b + u) * step];
+#pragma unroll
+    for (int u = 0; u < 8; u++) sum += v[u];
+  }
+  for (; b < count; b++) sum += p[(size_t)b * step];
   dst[row * dst_stride + map.off[t]] += sum;
 }
 
