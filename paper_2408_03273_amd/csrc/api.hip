@@ -669,9 +669,16 @@ ewald_status_t join_to(ewald_plan* pl, hipStream_t from, hipStream_t to) {
 //   against 330;
 //   real space over many pairs: 40 sites x 35 000 atoms 245 against 343 (296,
 //   346), 400 x 5000 270 against 345 (330, 357), 200 x 19 200 with half the box
-//   in reach 532 against 453, 80 x 60 000 with all of it 442 against 384.
+//   in reach 532 against 453, 80 x 60 000 with all of it 442 against 384;
+//   deterministic plans, whose MM side of real space takes the sites one after
+//   another in each thread (1.2 us per site, with images for each of eight): 40 sites x 35 000
+//   atoms 313 against 357, 150 x 1500 305 and 324, 200 x 5000 430 and 337, 300 x 500 488 and
+//   416, and with gradients of the field outputs 60 x 20 000 540 and 523, 80 x 20 000 642
+//   and 563.
 bool frame_one_stream(const ewald_plan* pl, const Seq& q) {
   if ((double)q.max_nq * q.max_nm > 2.5e6) return false;
+  if (pl->w.det_real && (q.max_nq * (q.mm_groups > 0 ? 8 : 1) > 100 || (double)q.max_nq * q.max_nm > 1.1e6))
+    return false;
   const Mesh& m = pl->mesh;
   if (q.mesh) return q.max_nm + (double)m.N[0] * m.N[1] * m.N[2] / 60.0 < 55000.0;
   return (double)q.max_nm * pl->g.KF < (pl->t.fp32r ? 1.3e9 : 6.5e8);
