@@ -738,7 +738,7 @@ ewald_status_t seq_fwd_bwd(const Seq& q, hipStream_t aux, hipStream_t aux2, cons
       // adjoint hot loop follows as soon as the MM tables are ready
       LCHK(launch_prep(g, q.fa, q.max_nq, q.max_nm, qm_xyz, Q, mu, theta, mm_xyz, mm_q, w, q.s, pl->cap_qm,
                        pl->cap_mm, tables, 1, PREP_QM_TAB));
-      LCHK(launch_sfac_qm(g, q.fa, q.max_nq, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, 1, w, q.s));
+      LCHK(launch_sfac_qm(g, q.fa, q.max_nq, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, 1, q.qmqm, w, q.s));
       if (overlap) HIPCHK(hipEventRecord(pl->ev_qside, q.s));
     }
   }
@@ -1097,7 +1097,7 @@ ewald_status_t ewald_forward(ewald_plan* plan, int n_qm, const double* qm_xyz, c
     hipError_t e;
     {
       ProfScope ps(plan, "launch_sfac_qm", s);
-      e = launch_sfac_qm(plan->g, q.fa, n_qm, Q, mu, theta, plan->w.qeff, 0, 0, plan->w, s);
+      e = launch_sfac_qm(plan->g, q.fa, n_qm, Q, mu, theta, plan->w.qeff, 0, 0, q.qmqm, plan->w, s);
     }
     if (e != hipSuccess) st = fail(EWALD_ERR_HIP, "sfac_qm launch: %s", hipGetErrorString(e));
   }
@@ -1192,7 +1192,7 @@ ewald_status_t ewald_backward(ewald_plan* plan, const void* ctx, int n_qm, const
     return st;
   }
   STEP(launch_eff_moments(q.fa, n_qm, Q, mu, theta, gE, g_phi, g_efield, g_efgrad, w, s));
-  STEP(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, 0, w, s));
+  STEP(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, q.mesh ? 1 : 2, 0, 0, w, s));
   if (q.mesh) {
     STEP(launch_mesh_sort(plan->mesh, q.fa, n_mm, plan->cap_mm, w, s));
     STEP(launch_mesh_force(plan->mesh, g, q.fa, n_mm, w, s));
@@ -1276,7 +1276,7 @@ ewald_status_t enqueue_batch(ewald_plan* plan, hipStream_t s, int n_frames, int 
   }
   ewald_status_t st = seq_begin(q, qm_xyz, Q, mu, theta, mm_xyz, mm_q, mesh ? 0 : mm_tables_for(pl), 0);
   if (st != EWALD_OK) return st;
-  LCHK(launch_sfac_qm(g, q.fa, max_nq, Q, mu, theta, w.qeff, 0, 0, w, s));
+  LCHK(launch_sfac_qm(g, q.fa, max_nq, Q, mu, theta, w.qeff, 0, 0, q.qmqm, w, s));
   if (mesh) {
     LCHK(launch_mesh_sort(pl->mesh, q.fa, max_nm, pl->cap_mm, w, s));
     LCHK(launch_mesh_sfac(pl->mesh, q.fa, w, s));
@@ -1516,7 +1516,7 @@ extern "C" ewald_status_t ewald_moments_update(ewald_plan* plan, const void* ctx
   plan->stale_ctx.insert(ctx);
   st = seq_begin(q, qm_xyz, Q, mu, theta, nullptr, nullptr, 0, 1);
   if (st != EWALD_OK) return st;
-  LCHK(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, 0, 0, w, s));
+  LCHK(launch_sfac_qm(g, q.fa, n_qm, Q, mu, theta, w.qeff, 0, 0, q.qmqm, w, s));
   if (q.qmqm && n_qm > 0) {
     LCHK(launch_project_qm(g, q.fa, n_qm, nullptr, 0, Q, mu, theta, 1, 1, w, s));
     LCHK(launch_qmqm(g, q.fa, n_qm, plan->cap_qm, Q, mu, theta, w, s));
@@ -1856,7 +1856,7 @@ extern "C" ewald_status_t ewald_autotune(ewald_plan* plan, int n_mm, const char*
     q.fa.n_frames = 1;
     st = seq_begin(q, dqp, dQ, dmu, dth, dm, dq, 2, 1);
     if (st != EWALD_OK) goto done;
-    TCHK(launch_sfac_qm(plan->g, q.fa, nq, dQ, dmu, dth, plan->w.qeff, 2, 0, plan->w, s));
+    TCHK(launch_sfac_qm(plan->g, q.fa, nq, dQ, dmu, dth, plan->w.qeff, 2, 0, 0, plan->w, s));
     auto time_it = [&](auto&& launch) -> double {
       hipError_t e = launch();  // warm-up
       if (e != hipSuccess) return -1.0;

@@ -259,9 +259,10 @@ hipError_t launch_prep(const Grid& g, const FrameArg& fa, int max_nq, int max_nm
                        const double* mm_q, Work& w, hipStream_t s, int cap_qm, int cap_mm, int mm_tables,
                        int unit_eff, int parts = PREP_ALL);
 // with_w: 0 no adjoint weights, 1 in k order, 2 also in matrix-core operand order;
-// unit: the effective moments are the moments themselves
+// unit: the effective moments are the moments themselves; qq: sum the QM-QM energy
 hipError_t launch_sfac_qm(const Grid& g, const FrameArg& fa, int max_nq, const double* Q, const double* mu,
-                          const double* theta, const double* qeff, int with_w, int unit, Work& w, hipStream_t s);
+                          const double* theta, const double* qeff, int with_w, int unit, int qq, Work& w,
+                          hipStream_t s);
 hipError_t launch_sfac_mm(const Grid& g, const Tuning& t, const FrameArg& fa, int max_nm, int cap_mm, Work& w,
                           hipStream_t s);
 // gridded reciprocal sums (mesh.hip): atoms sorted into bins with their kernel

@@ -432,7 +432,8 @@ static void launch_tab(const Grid& g, const FrameArg& fa, int qm_side, int with_
 // Forward and adjoint for an upstream gradient of 1 (unit): S' = A + B + C, not
 // summed again (16 frames of 80 sites at kmax 32: 337 -> 236 us).
 // The reciprocal part of the order-2 truncated QM-QM image energy,
-// (4 pi/V) g (|A|^2 + 2 Re A*B + 2 Re A*C + |B|^2), is summed along the way.
+// (4 pi/V) g (|A|^2 + 2 Re A*B + 2 Re A*C + |B|^2), is summed along the way where the
+// call wants it (facc not null).
 DEV void qm_terms(double (&v)[8], double2 e, double Qj, double kmu, double kthk) {
   v[0] += Qj * e.x;
   v[1] += Qj * e.y;
@@ -534,12 +535,14 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
       if (with_w) wk[(size_t)f * g.KF + k] = W[sg];
     }
   }
-  eqq = wave_sum(eqq);
-  if (lane == 0) {
-    if (det)
-      det[(size_t)f * gridDim.x + blockIdx.x] = eqq;
-    else
-      atomicAdd(&facc[f * FA_COUNT + FA_E_QQ_LR], eqq);
+  if (facc) {
+    eqq = wave_sum(eqq);
+    if (lane == 0) {
+      if (det)
+        det[(size_t)f * gridDim.x + blockIdx.x] = eqq;
+      else
+        atomicAdd(&facc[f * FA_COUNT + FA_E_QQ_LR], eqq);
+    }
   }
   if (live && with_w && wfrag) {
     if (p == 0) {
@@ -570,16 +573,17 @@ __global__ __launch_bounds__(256) void k_sfac_qm(Grid g, FrameArg fa, const doub
 }
 
 hipError_t launch_sfac_qm(const Grid& g, const FrameArg& fa, int max_nq, const double* Q, const double* mu,
-                          const double* theta, const double* qeff, int with_w, int unit, Work& w, hipStream_t s) {
+                          const double* theta, const double* qeff, int with_w, int unit, int qq, Work& w,
+                          hipStream_t s) {
   (void)max_nq;
   dim3 grid((g.NCOL * (g.mz + 1) + 63) / 64, fa.n_frames);
   // with_w: 1 the adjoint weights in k order (gridded adjoint), 2 also in matrix-core order
   hipLaunchKernelGGL(k_sfac_qm, grid, dim3(256), 0, s, g, fa, Q, mu, theta, qeff, w.qm_tab, with_w, unit,
                      w.sabc, w.wk,
-                     w.kw, with_w == 2 ? w.wfrag : (double*)nullptr, w.wk0, w.facc, w.det_qqlr);
+                     w.kw, with_w == 2 ? w.wfrag : (double*)nullptr, w.wk0, qq ? w.facc : (double*)nullptr, w.det_qqlr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (w.det_qqlr) {
+  if (qq && w.det_qqlr) {
     e = launch_det_reduce(fa, 0, 1, w.det_qqlr, (int)grid.x, 1, det_map({FA_E_QQ_LR}), w.facc, FA_COUNT, s);
     if (e != hipSuccess) return e;
   }
